@@ -93,10 +93,11 @@ typedef struct vpp_chunk_attn_plan_s* vpp_chunk_attn_plan_t;
  *
  * *inout_plan == NULL creates a plan (owned by the library until
  * vpp_chunk_attn_destroy); a non-NULL plan is refilled in place with the same
- * config (cfg may be NULL then). Refilling never blocks: each run copies the
- * work list to the device from a pinned staging slot of its own (a ring of 4
- * per plan), and only a run that reuses a slot whose earlier copy is still in
- * flight waits, on the host, for that copy.
+ * config (cfg may be NULL then). Refilling never blocks: a run hands its launch
+ * table (one entry per segment and split piece) to the kernel in the kernel
+ * arguments, or, past 64 entries, copies it to the device from a pinned staging
+ * slot of its own (a ring of 4 per plan); only a run that reuses a slot whose
+ * earlier copy is still in flight waits, on the host, for that copy.
  * *workspace_bytes receives the bytes of device workspace vpp_chunk_attn_run
  * needs for this plan (always > 0). The arrays are not retained.
  */
@@ -108,9 +109,9 @@ vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg,
 
 /*
  * Run a planned chunk, asynchronously on `stream` (a hipStream_t; NULL is the
- * default stream). Enqueues, in order: the copy of the plan's work list into
- * the workspace, the attention kernel, and -- when the plan splits the key
- * range -- the merge kernel. Never synchronizes the stream. All pointers are
+ * default stream). Enqueues, in order: for plans of more than 64 segments and
+ * split pieces the copy of the launch table into the workspace, the attention
+ * kernel, and -- when the plan splits a segment's key range -- the merge kernel. Never synchronizes the stream. All pointers are
  * caller-owned device memory that must stay valid until the stream reaches the
  * end of this work; lse may be NULL. The workspace (>= the planned bytes,
  * 256-byte aligned) must not be used by other work in flight.
@@ -134,13 +135,14 @@ vpp_status_t vpp_chunk_attn_run(vpp_chunk_attn_plan_t plan,
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc). Same plan, kernels, arguments and results
  * as vpp_chunk_attn_run: the same bits, split key ranges included. Its
- * workspace (the work list and, in split plans, the fp32 partials) is a static
+ * workspace (the launch table and, in split plans, the fp32 partials) is a static
  * device array of VPP_NOALLOC_SCRATCH_BYTES on the current device, whose
  * address the library looks up on its first call on that device. This call
- * makes no hipMalloc, hipFree, host-pinning or other allocating call: the work
- * list is copied to the device straight from the plan, whose host memory is
- * not pinned; HIP performs such a copy synchronously, so it is complete when
- * the call returns and the plan may be refilled at once. Nothing in the scratch
+ * makes no hipMalloc, hipFree, host-pinning or other allocating call: a launch
+ * table of up to 64 entries travels in the kernel arguments, a longer one is
+ * copied to the device straight from the plan, whose host memory is not pinned;
+ * HIP performs such a copy synchronously, so either way the plan may be refilled
+ * as soon as the call returns. Nothing in the scratch
  * needs clearing between calls: every byte a run reads, the same run writes
  * first.
  * The array used is the current device's (hipGetDevice at the call): the
@@ -254,8 +256,8 @@ vpp_status_t vpp_paged_slot_mapping(int32_t num_segments, const int32_t* cu_q,
                                     int32_t pages_per_row, int32_t page_size,
                                     int64_t* slot_mapping);
 
-/* Free a plan (NULL is ignored). Waits for the device to finish reading its
- * work list first. */
+/* Free a plan (NULL is ignored). Waits first for copies of its launch table
+ * that are still in flight. */
 void vpp_chunk_attn_destroy(vpp_chunk_attn_plan_t plan);
 
 /* Static text for a status value. */
@@ -277,8 +279,8 @@ typedef struct {
 vpp_status_t vpp_chunk_attn_plan_info(vpp_chunk_attn_plan_t plan,
                                       vpp_chunk_attn_plan_info_t* info);
 
-/* One planned work item, as the kernel reads it (rows and keys in
- * in-request coordinates). */
+/* One planned work item: a query tile and its keys (rows and keys in in-request
+ * coordinates). */
 typedef struct {
     int32_t row0;      /* first chunk row of the tile                         */
     int32_t nrows;     /* rows in the tile (1 .. block_m)                      */
@@ -294,7 +296,8 @@ typedef struct {
  * workgroup per head runs: the first entry's tile with its keys ascending, then
  * the second's (the partner tile from the other end of the same segment, in the
  * same split piece) with its keys descending. A second entry with nrows = 0 is
- * empty. Every (tile, split piece) appears exactly once. */
+ * empty. Every (tile, split piece) appears exactly once; a piece without keys
+ * (key_begin == key_end) is not launched. */
 vpp_status_t vpp_chunk_attn_plan_items(vpp_chunk_attn_plan_t plan,
                                        vpp_chunk_attn_work_item_t* items,
                                        int32_t capacity, int32_t* count);

@@ -125,26 +125,49 @@ static_assert(sizeof(WorkItem) == 32, "work item layout");
 // the kernels (the build compiles this file once per part, in parallel).
 namespace vpp_detail {
 
+// One launch group: the workgroups of one split piece of one segment, all heads
+// and work slots. Groups are contiguous runs of the grid, longest first.
+struct LaunchGroup {
+    int32_t wg0;        // the group's first workgroup
+    int32_t row0;       // first chunk row of the segment
+    int32_t len;        // rows of the segment
+    int32_t prefix;     // in-request position of the first row
+    int32_t kv_start;   // cache row of the request's position 0
+    int32_t key_begin;  // keys [key_begin, key_end) of the request; the last piece
+    int32_t key_end;    // (INT32_MAX) runs on to each tile's own end
+    int32_t seg;        // block-table row (paged cache)
+    int32_t part0;      // first row of the piece's fp32 partials; < 0: final results
+    int32_t slots;      // work slots per head: two tiles each, or one when slots == tiles
+};
+// A chunk of up to INLINE_GROUPS groups (16 segments with 4 pieces each, or any
+// one segment) carries its table in the kernel arguments: the 2.5 KB travel with
+// the dispatch packet, where an upload of its own costs a copy of 2 us and the
+// gaps around it, 12 to 15 us a run. Kernel arguments end at 4 KB.
+constexpr int INLINE_GROUPS = 64;
+struct GroupTable {
+    LaunchGroup g[INLINE_GROUPS];
+};
+
 struct AttnArgs {
-    const WorkItem* items;
+    const LaunchGroup* groups;  // table in device memory; null: the second kernel argument
+    int32_t num_groups;
+    int32_t num_heads;
     const u16* q;
     const u16* k;
     const u16* v;
-    void* out;   // bf16 [tokens][Hq][DV]; split mode: fp32 partials [splits][tokens][Hq][DV]
-    float* lse;  // fp32, h*lse_sh + row (nullable); split mode: partials [splits][Hq][tokens]
+    u16* out;         // bf16, row*o_st + h*o_sh
+    float* lse;       // fp32, h*lse_sh + row (nullable)
+    float* part_o;    // fp32 partials of split segments [partial row][Hq][DV]
+    float* part_lse;  // [partial row][Hq]
     // element strides (the host checks that they fit in 31 bits)
     int32_t q_st, q_sh, k_st, k_sh, v_st, v_sh, o_st, o_sh, lse_sh;
-    int32_t num_slots;  // work slots (two work-list entries each); the grid is num_slots x num_heads
-    int32_t num_entries;  // work-list entries: no entry at or past this index is read
-    int32_t num_heads;
     int32_t group;     // Hq / Hkv
-    int32_t tokens;    // chunk rows (partial layout)
     float scale_log2;  // softmax scale * log2(e)
     int32_t xcd_remap;
     // Paged cache (PAGED kernels only). Cache row j of segment s is row
     // j & (2^page_shift - 1) of page block_table[s * bt_st + (j >> page_shift)];
-    // the work item's kv_base carries (s << 32) | its first cache row, a multiple
-    // of the key tile, so no tile straddles a page (pages hold >= 64 rows).
+    // kv_start is a multiple of the key tile, so no tile straddles a page (pages
+    // hold >= 64 rows).
     const int32_t* block_table;
     int64_t bt_st;
     int64_t k_sp, v_sp;  // element strides between pages
@@ -156,21 +179,38 @@ struct AttnArgs {
     int32_t kr_st;
 };
 
-// Arguments of the merge of split partials.
+// The merge of split partials: one entry per split segment, covering the
+// workgroups from block0 on. Piece b of the segment's row r is partial row
+// part0 + b*len + r.
+struct CombineSeg {
+    int32_t block0, row0, len, pieces, part0;
+};
+struct CombineTable {
+    CombineSeg s[INLINE_GROUPS];
+};
 struct CombineArgs {
+    const CombineSeg* segs;  // table in device memory; null: the second kernel argument
     const float* part_o;
     const float* part_lse;
     u16* out;
     float* lse;
     int64_t o_st, o_sh, lse_sh;
-    int32_t tokens, num_heads, splits;
+    int32_t num_segs, num_heads, blocks;
 };
 
-hipError_t launch_attn_contig(int nb, int dqk, const AttnArgs& a, bool split, const CombineArgs& ca,
-                              hipStream_t stream);
-hipError_t launch_attn_paged(int nb, int dqk, const AttnArgs& a, bool split, const CombineArgs& ca,
-                             hipStream_t stream);
-hipError_t launch_attn_rope(int nb, const AttnArgs& a, bool split, const CombineArgs& ca, hipStream_t stream);
+// A planned launch: both kernels' arguments and grids (merge.blocks = 0: no merge).
+struct Launch {
+    AttnArgs a;
+    GroupTable groups;
+    CombineArgs merge;
+    CombineTable segs;
+    int32_t nb, dqk;
+    int64_t workgroups;
+};
+
+hipError_t launch_attn_contig(const Launch& l, hipStream_t stream);
+hipError_t launch_attn_paged(const Launch& l, hipStream_t stream);
+hipError_t launch_attn_rope(const Launch& l, hipStream_t stream);
 
 }  // namespace vpp_detail
 
@@ -178,6 +218,12 @@ namespace {
 
 using vpp_detail::AttnArgs;
 using vpp_detail::CombineArgs;
+using vpp_detail::CombineSeg;
+using vpp_detail::CombineTable;
+using vpp_detail::GroupTable;
+using vpp_detail::Launch;
+using vpp_detail::LaunchGroup;
+using vpp_detail::INLINE_GROUPS;
 
 // LDS tiles: K [BN][DQK] and V [BN][DV] bf16, row-major in 16-byte granules,
 // the granule index XOR-swizzled per row. The LDS serves 64 banks (256 bytes)
@@ -245,19 +291,47 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-// Launch-order index -> (slot, head). With remapping on, the hardware's
-// round-robin placement of consecutive workgroups on the 8 XCDs is undone so
-// that each XCD runs a contiguous run of logical work (the slots of the same
-// heads, which read the same K/V through that XCD's L2).
-__device__ __forceinline__ void work_coords(const AttnArgs& a, int& slot, int& head) {
-    const int64_t total = (int64_t)a.num_slots * a.num_heads;
-    int64_t L = blockIdx.x;
-    if (a.xcd_remap) {
-        const int64_t per = total / 8;
-        if (L < per * 8) L = (L % 8) * per + L / 8;
+// Tables that travel in the kernel arguments or in device memory, read as
+// constant memory: uniform indices become scalar loads.
+typedef __attribute__((address_space(4))) const LaunchGroup const_group_t;
+typedef __attribute__((address_space(4))) const CombineSeg const_seg_t;
+template <typename T>
+__device__ __forceinline__ T* const_ptr(uint64_t p) {
+    return (T*)(uintptr_t)p;
+}
+
+// Index of the last of `n` table entries (bytes `stride` apart, their first word
+// ascending and the first entry's <= x) whose first word is <= x. Each step
+// compares 64 of them at once, one per lane: one step up to 64 entries, two up to
+// 4096.
+__device__ __forceinline__ int find_entry(uint64_t table, int stride, int n, int x) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, cnt = n;
+    while (cnt > 1) {
+        const int step = (cnt + 63) >> 6;
+        const int off = lane * step;
+        const int idx = lo + min(off, cnt - 1);
+        const int first = *(__attribute__((address_space(1))) const int32_t*)(uintptr_t)(table + (uint64_t)idx * stride);
+        const int p = __popcll(__builtin_amdgcn_ballot_w64(off < cnt && first <= x)) - 1;
+        lo += p * step;
+        cnt = min(step, cnt - p * step);
     }
-    head = (int)(L / a.num_slots);
-    slot = (int)(L % a.num_slots);
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// Workgroup i of a group -> (slot, head). Consecutive workgroups land on the 8
+// XCDs round robin; the remap gives each XCD a contiguous run of the group's
+// head-major order (the slots of the same heads, which read the same K/V through
+// that XCD's L2). Every group is spread over all XCDs, so a long group loads
+// them alike.
+__device__ __forceinline__ void work_coords(int i, int slots, int heads, bool remap, int& slot, int& head) {
+    if (remap) {
+        const int n = slots * heads;
+        const int x = i & 7;
+        i = x * (n >> 3) + min(x, n & 7) + (i >> 3);
+    }
+    head = i / slots;
+    slot = i - head * slots;
 }
 
 template <int DQK, int DV, int NB>
@@ -516,9 +590,9 @@ __device__ __forceinline__ void static_range(F&& f) {
 // KV_PAGED: the same rows in pages reached through a block table; KV_ROPE
 // (dqk = 192 only): K split into a per-head part k_nope [rows][Hkv][128] and a
 // part shared by all heads k_rope [rows][64], the key layout of the MLA models.
-template <int DQK, int DV, int NB, bool SPLIT, int KVM>
+template <int DQK, int DV, int NB, int KVM>
 __global__ __attribute__((amdgpu_flat_work_group_size(NTHREADS, NTHREADS), amdgpu_waves_per_eu(3 - NB, 3 - NB)))
-void attn_fwd_kernel(AttnArgs a) {
+void attn_fwd_kernel(AttnArgs a, GroupTable) {
     constexpr bool PAGED = KVM == KV_PAGED;
     constexpr bool ROPE = KVM == KV_ROPE;
     static_assert(!ROPE || DQK == 192, "the split key layout is 128 + 64 dims");
@@ -536,26 +610,32 @@ void attn_fwd_kernel(AttnArgs a) {
     char* const kbuf0 = smem;
     char* const vbuf0 = smem + 2 * T::K_BYTES;
 
+    constexpr int BM = block_rows(NB);
+    // this workgroup's launch group; the inline table follows the first argument
+    auto group_base = [](const LaunchGroup* table) {
+        return table ? (uint64_t)(uintptr_t)table
+                     : (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(AttnArgs);
+    };
+    const int gidx = find_entry(group_base(a.groups), sizeof(LaunchGroup), a.num_groups, (int)blockIdx.x);
+    const_group_t* const grp = const_ptr<const_group_t>(group_base(a.groups)) + gidx;
+    const int slots = grp->slots;
     int slot, h;
-    work_coords(a, slot, h);
-    // A slot holds up to two tiles: the first runs its key range ascending, the
-    // second (if any) descending; an empty second entry has no rows.
+    work_coords((int)blockIdx.x - grp->wg0, slots, a.num_heads, a.xcd_remap != 0, slot, h);
+    const int seg_tiles = (grp->len + BM - 1) / BM;
+    // A slot holds up to two tiles of the segment: the first runs its key range
+    // ascending, its partner from the other end (if any) descending.
 #pragma nounroll
     for (int sub = 0; sub < 2; ++sub) {
-        const int item_id = 2 * slot + sub;
-        if (item_id >= a.num_entries) break;
-        // the work item is uniform: keep it in SGPRs (so buffer resources built
-        // from it are scalar too)
-        WorkItem it = a.items[item_id];
-        it.row0 = __builtin_amdgcn_readfirstlane(it.row0);
-        it.nrows = __builtin_amdgcn_readfirstlane(it.nrows);
-        it.pos0 = __builtin_amdgcn_readfirstlane(it.pos0);
-        it.key_begin = __builtin_amdgcn_readfirstlane(it.key_begin);
-        it.key_end = __builtin_amdgcn_readfirstlane(it.key_end);
-        it.split = __builtin_amdgcn_readfirstlane(it.split);
-        it.kv_base = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(it.kv_base >> 32)) << 32) |
-                               (uint32_t)__builtin_amdgcn_readfirstlane((int)it.kv_base));
-        if (it.nrows == 0) break;
+        const int ti = sub == 0 ? slot : seg_tiles - 1 - slot;
+        if (sub == 1 && (slots == seg_tiles || ti == slot)) break;
+        const int t_row0 = ti * BM;  // the tile's first row in the segment
+        struct { int row0, nrows, pos0, key_begin, key_end; } it;
+        it.row0 = grp->row0 + t_row0;
+        it.nrows = min(BM, grp->len - t_row0);
+        it.pos0 = grp->prefix + t_row0;
+        it.key_begin = grp->key_begin;
+        it.key_end = min(grp->key_end, it.pos0 + it.nrows);
+        const int64_t kv_start = grp->kv_start;
         // every wave is done with the LDS tiles of the slot's previous tile before
         // this tile's first copies overwrite them
         lds_barrier();
@@ -568,7 +648,7 @@ void attn_fwd_kernel(AttnArgs a) {
 
         const int kb = it.key_begin, ke = it.key_end;
         // contiguous cache: the request's row 0 of head hk; paged: page 0's row 0
-        const int64_t cache_row0 = PAGED ? 0 : it.kv_base;
+        const int64_t cache_row0 = PAGED ? 0 : kv_start;
         const u16* kbase = a.k + cache_row0 * a.k_st + (int64_t)hk * a.k_sh;
         const u16* vbase = a.v + cache_row0 * a.v_st + (int64_t)hk * a.v_sh;
         const int ntiles = (ke - kb + BN - 1) / BN;
@@ -578,8 +658,8 @@ void attn_fwd_kernel(AttnArgs a) {
         const int dkt = rev ? -BN : BN;
         const int kt_first = rev ? kb + (ntiles - 1) * BN : kb;
         // paged cache: this segment's block-table row and the cache row of key 0
-        const int32_t* bt_row = PAGED ? a.block_table + (int64_t)(int32_t)(it.kv_base >> 32) * a.bt_st : nullptr;
-        const int kv_off = PAGED ? (int)(uint32_t)it.kv_base : 0;
+        const int32_t* bt_row = PAGED ? a.block_table + (int64_t)grp->seg * a.bt_st : nullptr;
+        const int kv_off = PAGED ? (int)kv_start : 0;
         const int pmask = PAGED ? (1 << a.page_shift) - 1 : 0;
         const int last_row = kv_off + ke - 1;  // page reads past the key range are clamped here
         auto clamp_page = [&](int pg) { return (int)min((uint32_t)pg, (uint32_t)(a.num_pages - 1)); };
@@ -1042,9 +1122,9 @@ void attn_fwd_kernel(AttnArgs a) {
         // they do not occupy scalar registers across the key loop.
         const AttnArgs* ka = (const AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(ka));
-        const WorkItem it2 = ka->items[item_id];
-        const int row0 = __builtin_amdgcn_readfirstlane(it2.row0);
-        const int split = __builtin_amdgcn_readfirstlane(it2.split);
+        const_group_t* const g2 = const_ptr<const_group_t>(group_base(ka->groups)) + gidx;
+        const int part0 = g2->part0;
+        const int row0 = (part0 >= 0 ? part0 : g2->row0) + t_row0;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const float l_tot = lane_swap32_add(l_part[nb]);
@@ -1052,8 +1132,9 @@ void attn_fwd_kernel(AttnArgs a) {
             const float lse_val = l_tot > 0.f ? (m_run[nb] + __log2f(l_tot)) * 0.69314718055994531f : -INFINITY;
             if (!qvalid[nb]) continue;
             const int row = row0 + wave * WROWS + nb * 32 + lr;
-            if constexpr (SPLIT) {
-                float* po = (float*)ka->out + (((int64_t)split * ka->tokens + row) * ka->num_heads + h) * DV;
+            if (part0 >= 0) {
+                const int64_t prow = (int64_t)row * ka->num_heads + h;
+                float* po = ka->part_o + prow * DV;
 #pragma unroll
                 for (int d = 0; d < DB; ++d)
 #pragma unroll
@@ -1062,9 +1143,9 @@ void attn_fwd_kernel(AttnArgs a) {
                                     o[d][nb][c * 4 + 2] * inv_l, o[d][nb][c * 4 + 3] * inv_l};
                         *(float4*)(po + d * 32 + c * 8 + lg * 4) = w;
                     }
-                if (lg == 0) ka->lse[((int64_t)split * ka->num_heads + h) * ka->tokens + row] = lse_val;
+                if (lg == 0) ka->part_lse[prow] = lse_val;
             } else {
-                u16* op = (u16*)ka->out + (int64_t)row * ka->o_st + (int64_t)h * ka->o_sh;
+                u16* op = ka->out + (int64_t)row * ka->o_st + (int64_t)h * ka->o_sh;
 #pragma unroll
                 for (int d = 0; d < DB; ++d)
 #pragma unroll
@@ -1077,104 +1158,94 @@ void attn_fwd_kernel(AttnArgs a) {
                 if (lg == 0 && ka->lse) ka->lse[(int64_t)h * ka->lse_sh + row] = lse_val;
             }
         }
-    }  // slot entries
+    }  // slot tiles
 }
 
 
-// Merge of split partials: lse = log sum_s exp(lse_s); out = sum_s exp(lse_s - lse) O_s.
+// Merge of split partials: lse = log sum_b exp(lse_b); out = sum_b exp(lse_b - lse) O_b.
+// DV/4 threads per (row, head), 4 values each; a block stays within one segment.
 template <int DV>
-__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
-    constexpr int G = DV / 4;  // threads per (row, head): 4 values each
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t pair = gid / G;
-    const int c = (int)(gid % G);
-    if (pair >= (int64_t)a.tokens * a.num_heads) return;
+__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, CombineTable) {
+    constexpr int G = DV / 4;
+    const uint64_t table = a.segs ? (uint64_t)(uintptr_t)a.segs
+                                  : (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(CombineArgs);
+    const_seg_t* const sg = const_ptr<const_seg_t>(table) +
+                            find_entry(table, sizeof(CombineSeg), a.num_segs, (int)blockIdx.x);
+    const int len = sg->len, n = sg->pieces;
+    const int64_t pair = ((int64_t)((int)blockIdx.x - sg->block0) * 256 + threadIdx.x) / G;
+    const int c = (int)(threadIdx.x % G);
+    if (pair >= (int64_t)len * a.num_heads) return;
     const int row = (int)(pair / a.num_heads);
-    const int h = (int)(pair % a.num_heads);
-    float ls[MAX_SPLITS];
+    const int h = (int)(pair - (int64_t)row * a.num_heads);
+    const int64_t p0 = ((int64_t)sg->part0 + row) * a.num_heads + h;  // piece 0; pieces are `step` apart
+    const int64_t step = (int64_t)len * a.num_heads;
+    const float* const pl = a.part_lse + p0;
+    const float* const po = a.part_o + p0 * DV + c * 4;
     float mx = -INFINITY;
-    for (int s = 0; s < a.splits; ++s) {
-        ls[s] = a.part_lse[((int64_t)s * a.num_heads + h) * a.tokens + row];
-        mx = fmaxf(mx, ls[s]);
-    }
+    for (int b = 0; b < n; ++b) mx = fmaxf(mx, pl[b * step]);
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     float den = 0.f;
-    for (int s = 0; s < a.splits; ++s) {
-        const float w = (ls[s] == -INFINITY) ? 0.f : __expf(ls[s] - mx);
+    for (int b = 0; b < n; ++b) {
+        const float l = pl[b * step];
+        const float w = (l == -INFINITY) ? 0.f : __expf(l - mx);
         den += w;
-        const float4 v = *(const float4*)(a.part_o + (((int64_t)s * a.tokens + row) * a.num_heads + h) * DV + c * 4);
+        const float4 v = *(const float4*)(po + b * step * DV);
         acc[0] += w * v.x;
         acc[1] += w * v.y;
         acc[2] += w * v.z;
         acc[3] += w * v.w;
     }
     const float inv = 1.f / den;
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
     bf16x4 r;
 #pragma unroll
     for (int j = 0; j < 4; ++j) r[j] = (__bf16)(acc[j] * inv);
-    *(bf16x4*)(a.out + (int64_t)row * a.o_st + (int64_t)h * a.o_sh + c * 4) = r;
-    if (c == 0 && a.lse) a.lse[(int64_t)h * a.lse_sh + row] = mx + __logf(den);
+    const int64_t orow = (int64_t)sg->row0 + row;
+    *(bf16x4*)(a.out + orow * a.o_st + (int64_t)h * a.o_sh + c * 4) = r;
+    if (c == 0 && a.lse) a.lse[(int64_t)h * a.lse_sh + orow] = mx + __logf(den);
 }
 
 [[maybe_unused]] size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 template <int DQK, int DV, int NB, int KVM>
-hipError_t launch(const AttnArgs& a, bool split, const CombineArgs& ca, hipStream_t stream) {
-    const int64_t total = (int64_t)a.num_slots * a.num_heads;
-    if (total <= 0) return hipSuccess;
-    if (total > (int64_t)INT32_MAX) return hipErrorInvalidValue;
-    dim3 grid((unsigned)total), block(NTHREADS);
-    if (split) {
-        hipLaunchKernelGGL((attn_fwd_kernel<DQK, DV, NB, true, KVM>), grid, block, 0, stream, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        const int64_t threads = (int64_t)ca.tokens * ca.num_heads * (DV / 4);
-        dim3 cg((unsigned)((threads + 255) / 256));
-        hipLaunchKernelGGL((combine_kernel<DV>), cg, dim3(256), 0, stream, ca);
-    } else {
-        hipLaunchKernelGGL((attn_fwd_kernel<DQK, DV, NB, false, KVM>), grid, block, 0, stream, a);
-    }
+hipError_t launch(const Launch& l, hipStream_t stream) {
+    if (l.workgroups <= 0) return hipSuccess;
+    if (l.workgroups > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((attn_fwd_kernel<DQK, DV, NB, KVM>), dim3((unsigned)l.workgroups), dim3(NTHREADS), 0, stream,
+                       l.a, l.groups);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || l.merge.blocks == 0) return e;
+    hipLaunchKernelGGL((combine_kernel<DV>), dim3((unsigned)l.merge.blocks), dim3(256), 0, stream, l.merge, l.segs);
     return hipGetLastError();
 }
 
 template <int KVM>
-hipError_t launch_dims(int nb, int dqk, const AttnArgs& a, bool split, const CombineArgs& ca, hipStream_t stream) {
+hipError_t launch_dims(const Launch& l, hipStream_t stream) {
     if constexpr (KVM == KV_ROPE) {
         // the split key layout exists for dqk = 192 only (the caller checks)
-        if (nb == 1) return launch<192, 128, 1, KVM>(a, split, ca, stream);
-        return launch<192, 128, 2, KVM>(a, split, ca, stream);
+        if (l.nb == 1) return launch<192, 128, 1, KVM>(l, stream);
+        return launch<192, 128, 2, KVM>(l, stream);
     } else {
-        if (nb == 1) {
-            if (dqk == 64) return launch<64, 64, 1, KVM>(a, split, ca, stream);
-            if (dqk == 128) return launch<128, 128, 1, KVM>(a, split, ca, stream);
-            return launch<192, 128, 1, KVM>(a, split, ca, stream);
+        if (l.nb == 1) {
+            if (l.dqk == 64) return launch<64, 64, 1, KVM>(l, stream);
+            if (l.dqk == 128) return launch<128, 128, 1, KVM>(l, stream);
+            return launch<192, 128, 1, KVM>(l, stream);
         }
-        if (dqk == 64) return launch<64, 64, 2, KVM>(a, split, ca, stream);
-        if (dqk == 128) return launch<128, 128, 2, KVM>(a, split, ca, stream);
-        return launch<192, 128, 2, KVM>(a, split, ca, stream);
+        if (l.dqk == 64) return launch<64, 64, 2, KVM>(l, stream);
+        if (l.dqk == 128) return launch<128, 128, 2, KVM>(l, stream);
+        return launch<192, 128, 2, KVM>(l, stream);
     }
 }
 
 }  // namespace
 
 #if VPP_PART == 0 || VPP_PART == 3
-hipError_t vpp_detail::launch_attn_contig(int nb, int dqk, const AttnArgs& a, bool split,
-                                          const CombineArgs& ca, hipStream_t stream) {
-    return launch_dims<KV_CONTIG>(nb, dqk, a, split, ca, stream);
-}
+hipError_t vpp_detail::launch_attn_contig(const Launch& l, hipStream_t stream) { return launch_dims<KV_CONTIG>(l, stream); }
 #endif
 #if VPP_PART == 1 || VPP_PART == 3
-hipError_t vpp_detail::launch_attn_paged(int nb, int dqk, const AttnArgs& a, bool split,
-                                         const CombineArgs& ca, hipStream_t stream) {
-    return launch_dims<KV_PAGED>(nb, dqk, a, split, ca, stream);
-}
+hipError_t vpp_detail::launch_attn_paged(const Launch& l, hipStream_t stream) { return launch_dims<KV_PAGED>(l, stream); }
 #endif
 #if VPP_PART == 2 || VPP_PART == 3
-hipError_t vpp_detail::launch_attn_rope(int nb, const AttnArgs& a, bool split, const CombineArgs& ca,
-                                        hipStream_t stream) {
-    return launch_dims<KV_ROPE>(nb, 192, a, split, ca, stream);
-}
+hipError_t vpp_detail::launch_attn_rope(const Launch& l, hipStream_t stream) { return launch_dims<KV_ROPE>(l, stream); }
 #endif
 
 #if VPP_PART == 0 || VPP_PART == 3
@@ -1223,26 +1294,39 @@ __global__ __launch_bounds__(256) void kv_append_kernel(AppendArgs a) {
 // ---------------------------------------------------------------------------
 // host side: plan
 // ---------------------------------------------------------------------------
+// One segment with rows, cut into query tiles and split pieces. A work slot runs
+// two tiles (paired) or one; `pieces` cuts its prefix (see piece_bounds).
+struct SegPlan {
+    int32_t seg, row0, len, prefix, kv_start;
+    int32_t tiles, pieces;
+    bool paired;
+    int32_t slots() const { return paired ? (tiles + 1) / 2 : tiles; }
+};
+
 struct vpp_chunk_attn_plan_s {
     vpp_chunk_attn_config_t cfg;
     float scale;
-    std::vector<WorkItem> items;
-    std::vector<int32_t> item_seg;  // segment of each work item (paged runs)
-    int32_t num_slots = 0;          // workgroups per head: items.size() / 2
+    std::vector<SegPlan> segs;
+    std::vector<LaunchGroup> groups;  // launch order
+    std::vector<CombineSeg> merges;   // split segments
+    int32_t merge_blocks = 0;
+    int64_t workgroups = 0;
+    int64_t num_items = 0;  // work items of plan_items: two per slot and piece
+    int32_t num_slots = 0;
     int32_t num_tiles = 0;
     int32_t num_splits = 1;
     int32_t nb = 2;  // 32-row query blocks per wave of the kernel variant the plan was made for
     int32_t tokens = 0;
     double pairs = 0.0;
-    size_t items_bytes = 0;
+    size_t table_bytes = 0;  // groups, then merges, where they exceed the kernel arguments; else 0
+    size_t part_o_off = 0, part_lse_off = 0;  // of the partials in the workspace
     size_t ws_bytes = 0;
-    // pinned staging ring for the work-list copy, created on first run
-    WorkItem* staging[STAGING_SLOTS] = {};
+    // pinned staging ring for the table copy, created on the first run that needs it
+    char* staging[STAGING_SLOTS] = {};
     size_t staging_cap[STAGING_SLOTS] = {};
     hipEvent_t staging_done[STAGING_SLOTS] = {};
     bool staging_pending[STAGING_SLOTS] = {};
     int next_slot = 0;
-    int device = -1;
 };
 
 namespace {
@@ -1293,54 +1377,114 @@ int fixed_splits(const vpp_chunk_attn_config_t& c, int64_t max_prefix) {
 // Boundary b of the n-part split of a p-key prefix (tile-aligned, b = 0 .. n-1).
 int32_t piece_begin(int64_t p, int n, int b) { return (int32_t)(((p / BN) * b / n) * BN); }
 
+// Keys [begin, end) of piece b of n of a segment; end = INT32_MAX for the last.
+// A segment cut into fewer pieces than the plan's n has empty ones in front.
+void piece_bounds(const SegPlan& s, int n, int b, int32_t& begin, int32_t& end) {
+    const int skip = n - s.pieces;
+    begin = b <= skip ? 0 : piece_begin(s.prefix, s.pieces, b - skip);
+    end = b + 1 == n ? INT32_MAX : b < skip ? 0 : piece_begin(s.prefix, s.pieces, b + 1 - skip);
+}
+
+// Tile of slot `i` of a segment: the first (which = 0) or its partner; -1: none.
+int slot_tile(const SegPlan& s, int i, int which) {
+    if (which == 0) return i;
+    const int t = s.tiles - 1 - i;
+    return s.paired && t != i ? t : -1;
+}
+
+// Keys of tile t (bm rows) within [begin, end).
+int64_t tile_keys(const SegPlan& s, int bm, int t, int32_t begin, int32_t end) {
+    const int32_t own = s.prefix + std::min((t + 1) * bm, s.len);
+    return std::max(0, std::min(own, end) - begin);
+}
+
+// A (segment, piece) in launch order: keys of its longest slot.
+struct PieceRef {
+    int32_t si, b, begin, end;  // si: index into the segment plans
+    int64_t keys;
+};
+
+// Every piece of every segment, longest first; empty pieces too if `all`.
+std::vector<PieceRef> launch_order(const std::vector<SegPlan>& segs, int n, int bm, bool all) {
+    std::vector<PieceRef> v;
+    v.reserve(segs.size() * (size_t)n);
+    for (size_t k = 0; k < segs.size(); ++k) {
+        const SegPlan& s = segs[k];
+        for (int b = 0; b < n; ++b) {
+            PieceRef r{(int32_t)k, b, 0, 0, 0};
+            piece_bounds(s, n, b, r.begin, r.end);
+            if (!all && r.begin == r.end) continue;
+            // a paired slot's two tiles together span the same keys in every slot but
+            // the first (whose partner may be short) and the middle one
+            const int last = s.slots() - 1;
+            for (int i : {0, std::min(1, last), last}) {
+                int64_t keys = tile_keys(s, bm, i, r.begin, r.end);
+                const int t = slot_tile(s, i, 1);
+                if (t >= 0) keys += tile_keys(s, bm, t, r.begin, r.end);
+                r.keys = std::max(r.keys, keys);
+            }
+            v.push_back(r);
+        }
+    }
+    std::stable_sort(v.begin(), v.end(), [](const PieceRef& x, const PieceRef& y) { return x.keys > y.keys; });
+    return v;
+}
+
 // Automatic split count: simulate the launch of each candidate count and keep
-// the fastest. The grid is slots x heads, head-major, remapped so that XCD x
-// runs the x-th eighth of that order (work_coords); each XCD places its
-// workgroups in order on whichever of its CU slots frees first (32 CUs, times
-// the workgroups a CU holds). A workgroup costs its key tiles plus a fixed
-// amount per tile it runs (Q load, pipeline fill, store). A split count n > 1
-// also costs the fp32 partials its pieces write and the merge reads back. The
-// unsplit plan is kept whenever its simulated makespan is within 5 % of the
-// ideal (total work spread evenly), which covers every chunk with enough even
-// slots.
-template <typename Build>
+// the fastest. The grid is the groups in launch order, each group's workgroups
+// dealt to the 8 XCDs alike (work_coords); each XCD places its workgroups in order
+// on whichever of its CU slots frees first (32 CUs, times the workgroups a CU
+// holds). A workgroup costs its key tiles plus a fixed amount per tile it runs (Q
+// load, pipeline fill, store). A split count n > 1 also costs the fp32 partials
+// its pieces write and the merge reads back. The unsplit plan is kept whenever its
+// simulated makespan is within 5 % of the ideal (total work spread evenly), which
+// covers every chunk with enough even slots.
 int auto_split(const vpp_chunk_attn_config_t& c, int bm, int wg_per_cu, int64_t max_prefix, int32_t tokens,
-               Build&& build) {
+               std::vector<SegPlan>& segs) {
     constexpr int NXCD = 8, CU_PER_XCD = 32;
     constexpr double TILE_OVERHEAD = 2.0;  // fixed cost of a tile, in key tiles
     const int heads = c.num_q_heads;
     // one key tile of one workgroup: 2 bm BN (dqk + dv) flop at ~5 TFLOP/s per CU
     const double tile_s = 2.0 * bm * BN * (c.head_dim_qk + c.head_dim_v) / 5.0e12;
-    std::vector<WorkItem> list;
-    auto entry_cost = [](const WorkItem& w) {
-        return w.nrows ? (double)((w.key_end - w.key_begin + BN - 1) / BN) + TILE_OVERHEAD : 0.0;
-    };
+    auto entry_cost = [](int64_t keys) { return keys > 0 ? (double)((keys + BN - 1) / BN) + TILE_OVERHEAD : 0.0; };
     // simulated seconds of the launch, and of its work spread evenly over the chip
     auto simulate = [&](int n, double& ideal) {
-        build(n, list);
-        const int64_t nslots = (int64_t)list.size() / 2;
-        std::vector<double> cost((size_t)nslots);
-        double total = 0.0;
-        for (int64_t i = 0; i < nslots; ++i) {
-            cost[(size_t)i] = entry_cost(list[(size_t)(2 * i)]) + entry_cost(list[(size_t)(2 * i + 1)]);
-            total += cost[(size_t)i];
-        }
+        for (SegPlan& s : segs) s.pieces = n;
+        const std::vector<PieceRef> order = launch_order(segs, n, bm, false);
         const int lanes = CU_PER_XCD * wg_per_cu;
-        ideal = total * heads / (NXCD * lanes) * tile_s;
-        const int64_t all = nslots * heads, per = all / NXCD;
+        std::vector<std::vector<double>> costs;
+        double total = 0.0;
+        bool even = true;
+        for (const PieceRef& r : order) {
+            const SegPlan& s = segs[(size_t)r.si];
+            std::vector<double> v((size_t)s.slots());
+            for (int i = 0; i < s.slots(); ++i) {
+                v[(size_t)i] = entry_cost(tile_keys(s, bm, i, r.begin, r.end));
+                const int t = slot_tile(s, i, 1);
+                if (t >= 0) v[(size_t)i] += entry_cost(tile_keys(s, bm, t, r.begin, r.end));
+                total += v[(size_t)i] * heads;
+            }
+            even = even && (int64_t)s.slots() * heads % NXCD == 0;
+            costs.push_back(std::move(v));
+        }
+        ideal = total / (NXCD * lanes) * tile_s;
         double makespan = 0.0;
-        std::vector<double> free_at;
-        // with whole heads per XCD every XCD runs the same sequence: one suffices
-        const int xcds = heads % NXCD == 0 ? 1 : NXCD;
-        for (int x = 0; x < xcds; ++x) {
-            free_at.assign((size_t)lanes, 0.0);  // a min-heap of lane free times
-            auto place = [&](int64_t logical) {
-                std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
-                free_at.back() += cost[(size_t)(logical % nslots)];
-                std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
-            };
-            for (int64_t j = 0; j < per; ++j) place(x * per + j);
-            for (int64_t L = per * NXCD + x; L < all; L += NXCD) place(L);  // the part left unremapped
+        // with whole eighths of every group per XCD, all XCDs run alike
+        for (int x = 0; x < (even ? 1 : NXCD); ++x) {
+            std::vector<double> free_at((size_t)lanes, 0.0);  // a min-heap of lane free times
+            int64_t wg0 = 0;
+            for (const std::vector<double>& v : costs) {
+                const int64_t nwg = (int64_t)v.size() * heads;
+                const int64_t r = ((x - wg0) % NXCD + NXCD) % NXCD;  // residue of this XCD's share
+                const int64_t first = r * (nwg / NXCD) + std::min(r, nwg % NXCD);
+                const int64_t share = nwg / NXCD + (r < nwg % NXCD ? 1 : 0);
+                for (int64_t j = 0; j < share; ++j) {
+                    std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
+                    free_at.back() += v[(size_t)((first + j) % (int64_t)v.size())];
+                    std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
+                }
+                wg0 += nwg;
+            }
             makespan = std::max(makespan, *std::max_element(free_at.begin(), free_at.end()));
         }
         return makespan * tile_s;
@@ -1416,92 +1560,56 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
     // positions (the ascending front, and the descending one, which mirrors it), so
     // the tiles running side by side on one XCD share each K/V tile through its L2.
     // Slots are grouped by (segment, split piece); groups run longest first.
-    std::vector<WorkItem> items;
-    std::vector<int32_t> iseg;
+    std::vector<SegPlan> segs;
+    std::vector<LaunchGroup> groups;
+    std::vector<CombineSeg> merges;
     double pairs = 0.0;
-    int ntiles = 0, nsplit = 1;
+    int64_t ntiles = 0, nslots = 0, wgs = 0, part_rows = 0, blocks = 0;
+    int nsplit = 1;
     try {
-        struct Seg { int t0, t1; };  // the segment's tiles in `tiles`
-        std::vector<WorkItem> tiles;
-        std::vector<Seg> segs((size_t)num_segments);
         int64_t max_prefix = 0;
         for (int s = 0; s < num_segments; ++s) {
-            segs[s].t0 = (int)tiles.size();
-            for (int r0 = cu_q[s]; r0 < cu_q[s + 1]; r0 += BM) {
-                WorkItem w;
-                w.row0 = r0;
-                w.nrows = std::min(BM, cu_q[s + 1] - r0);
-                w.pos0 = (int32_t)(prefix_len[s] + (r0 - cu_q[s]));
-                w.key_begin = 0;
-                w.key_end = w.pos0 + w.nrows;
-                w.split = 0;
-                w.kv_base = kv_start[s];
-                tiles.push_back(w);
-                // visible pairs: sum over rows of (position + 1)
-                pairs += (double)w.nrows * (double)w.pos0 + 0.5 * (double)w.nrows * (w.nrows + 1);
-            }
-            segs[s].t1 = (int)tiles.size();
-            if (segs[s].t1 > segs[s].t0) max_prefix = std::max(max_prefix, prefix_len[s]);
+            const int32_t len = cu_q[s + 1] - cu_q[s];
+            if (len == 0) continue;
+            SegPlan sp{s, cu_q[s], len, (int32_t)prefix_len[s], (int32_t)kv_start[s], (int32_t)(((int64_t)len + BM - 1) / BM), 1, true};
+            // visible pairs: sum over rows of (position + 1)
+            pairs += (double)len * (double)prefix_len[s] + 0.5 * (double)len * (len + 1.0);
+            ntiles += sp.tiles;
+            nslots += sp.slots();
+            max_prefix = std::max(max_prefix, prefix_len[s]);
+            segs.push_back(sp);
         }
-        ntiles = (int)tiles.size();
+        if (!segs.empty())
+            nsplit = c.num_splits >= 1 ? fixed_splits(c, max_prefix)
+                                       : auto_split(c, BM, nb == 1 ? 2 : 1, max_prefix, cu_q[num_segments], segs);
+        for (SegPlan& s : segs) s.pieces = nsplit;
 
-        // the work list for n split pieces: two entries per slot, grouped by
-        // (segment, piece), longest group first
-        auto build = [&](int n, std::vector<WorkItem>& out, std::vector<int32_t>* out_seg) {
-            struct Group { int seg, piece; int64_t len; size_t first, count; };  // slots [first, first+count)
-            std::vector<Group> groups;
-            std::vector<WorkItem> grouped;  // two items per slot, group by group
-            const WorkItem none = {0, 0, 0, 0, 0, 0, 0};
-            for (int s = 0; s < num_segments; ++s) {
-                const int T = segs[s].t1 - segs[s].t0;
-                if (T == 0) continue;
-                for (int b = 0; b < n; ++b) {
-                    auto piece = [&](int ti) {
-                        WorkItem w = tiles[segs[s].t0 + ti];
-                        w.split = b;
-                        if (n > 1) {
-                            w.key_begin = piece_begin(prefix_len[s], n, b);
-                            if (b + 1 < n) w.key_end = piece_begin(prefix_len[s], n, b + 1);
-                        }
-                        return w;
-                    };
-                    Group g{s, b, 0, grouped.size() / 2, 0};
-                    for (int i = 0; i < (T + 1) / 2; ++i) {
-                        const WorkItem x = piece(i);
-                        const WorkItem y = (T - 1 - i != i) ? piece(T - 1 - i) : none;
-                        grouped.push_back(x);
-                        grouped.push_back(y);
-                        const int64_t len =
-                            (int64_t)(x.key_end - x.key_begin) + (y.nrows ? y.key_end - y.key_begin : 0);
-                        g.len = std::max(g.len, len);
-                        ++g.count;
-                    }
-                    groups.push_back(g);
-                }
+        // partial rows of the split segments, piece by piece; a segment with one piece
+        // that has keys writes its results directly
+        std::vector<int32_t> next_part(segs.size(), -1);
+        for (size_t k = 0; k < segs.size(); ++k) {
+            int pieces = 0;
+            for (int b = 0; b < nsplit; ++b) {
+                int32_t kb, ke;
+                piece_bounds(segs[k], nsplit, b, kb, ke);
+                pieces += kb != ke;
             }
-            std::stable_sort(groups.begin(), groups.end(),
-                             [](const Group& x, const Group& y) { return x.len > y.len; });
-            out.clear();
-            out.reserve(grouped.size());
-            if (out_seg) {
-                out_seg->clear();
-                out_seg->reserve(grouped.size());
-            }
-            for (const Group& g : groups)
-                for (size_t k = 0; k < 2 * g.count; ++k) {
-                    out.push_back(grouped[2 * g.first + k]);
-                    if (out_seg) out_seg->push_back(g.seg);
-                }
-        };
-        if (ntiles == 0) {
-            nsplit = 1;
-        } else if (c.num_splits >= 1) {
-            nsplit = fixed_splits(c, max_prefix);
-        } else {
-            nsplit = auto_split(c, BM, nb == 1 ? 2 : 1, max_prefix, cu_q[num_segments],
-                                [&](int n, std::vector<WorkItem>& out) { build(n, out, nullptr); });
+            if (pieces < 2) continue;
+            next_part[k] = (int32_t)part_rows;
+            merges.push_back({(int32_t)blocks, segs[k].row0, segs[k].len, pieces, (int32_t)part_rows});
+            part_rows += (int64_t)pieces * segs[k].len;
+            blocks += ((int64_t)segs[k].len * c.num_q_heads * (c.head_dim_v / 4) + 255) / 256;
         }
-        build(nsplit, items, &iseg);
+        for (const PieceRef& r : launch_order(segs, nsplit, BM, false)) {
+            const SegPlan& s = segs[(size_t)r.si];
+            LaunchGroup g{(int32_t)wgs, s.row0, s.len, s.prefix, s.kv_start, r.begin, r.end, s.seg, -1, s.slots()};
+            if (next_part[(size_t)r.si] >= 0) {
+                g.part0 = next_part[(size_t)r.si];
+                next_part[(size_t)r.si] += s.len;
+            }
+            groups.push_back(g);
+            wgs += (int64_t)g.slots * c.num_q_heads;
+        }
     } catch (const std::bad_alloc&) {
         return VPP_ERR_NOMEM;
     }
@@ -1514,21 +1622,26 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
     }
     p->nb = nb;
     p->scale = c.softmax_scale > 0.f ? c.softmax_scale : (float)(1.0 / sqrt((double)c.head_dim_qk));
-    p->items.swap(items);
-    p->item_seg.swap(iseg);
-    p->num_tiles = ntiles;
+    p->segs.swap(segs);
+    p->groups.swap(groups);
+    p->merges.swap(merges);
+    p->merge_blocks = (int32_t)blocks;
+    p->workgroups = wgs;
+    p->num_tiles = (int32_t)ntiles;
     p->num_splits = nsplit;
+    p->num_slots = (int32_t)(nslots * nsplit);
+    p->num_items = 2 * nslots * nsplit;
     p->tokens = cu_q[num_segments];
     p->pairs = pairs;
-    p->num_slots = (int32_t)(p->items.size() / 2);
-    p->items_bytes = p->items.size() * sizeof(WorkItem);
-    size_t ws = align256(std::max<size_t>(p->items_bytes, 1));
-    if (nsplit > 1) {
-        ws += align256((size_t)nsplit * p->tokens * c.num_q_heads * c.head_dim_v * sizeof(float));
-        ws += align256((size_t)nsplit * c.num_q_heads * p->tokens * sizeof(float));
-    }
-    p->ws_bytes = ws;
-    *workspace_bytes = ws;
+    p->table_bytes = p->groups.size() > INLINE_GROUPS || p->merges.size() > INLINE_GROUPS
+                         ? p->groups.size() * sizeof(LaunchGroup) + p->merges.size() * sizeof(CombineSeg)
+                         : 0;
+    // the workspace: the table (room for 32 bytes per work item), then the partials
+    const size_t head = align256(std::max<size_t>({p->table_bytes, (size_t)p->num_items * sizeof(WorkItem), 1}));
+    p->part_o_off = head;
+    p->part_lse_off = head + align256((size_t)part_rows * c.num_q_heads * c.head_dim_v * sizeof(float));
+    p->ws_bytes = p->part_lse_off + align256((size_t)part_rows * c.num_q_heads * sizeof(float));
+    *workspace_bytes = p->ws_bytes;
     return VPP_OK;
 }
 
@@ -1536,7 +1649,7 @@ extern "C" vpp_status_t vpp_chunk_attn_plan_info(vpp_chunk_attn_plan_t p, vpp_ch
     if (!p || !info) return VPP_ERR_INVALID_ARG;
     info->num_tiles = p->num_tiles;
     info->num_splits = p->num_splits;
-    info->num_work_items = (int32_t)p->items.size();
+    info->num_work_items = (int32_t)p->num_items;
     info->num_slots = p->num_slots;
     info->block_m = block_rows(p->nb);
     info->block_n = BN;
@@ -1549,9 +1662,33 @@ extern "C" vpp_status_t vpp_chunk_attn_plan_info(vpp_chunk_attn_plan_t p, vpp_ch
 extern "C" vpp_status_t vpp_chunk_attn_plan_items(vpp_chunk_attn_plan_t p, vpp_chunk_attn_work_item_t* items,
                                                   int32_t capacity, int32_t* count) {
     if (!p || !count || capacity < 0 || (capacity > 0 && !items)) return VPP_ERR_INVALID_ARG;
-    *count = (int32_t)p->items.size();
-    const int32_t n = std::min(capacity, *count);
-    if (n > 0) memcpy(items, p->items.data(), sizeof(WorkItem) * (size_t)n);
+    *count = (int32_t)p->num_items;
+    if (capacity == 0) return VPP_OK;
+    const int bm = block_rows(p->nb);
+    int32_t n = 0;
+    try {
+        for (const PieceRef& r : launch_order(p->segs, p->num_splits, bm, true)) {
+            const SegPlan& s = p->segs[(size_t)r.si];
+            for (int i = 0; i < s.slots(); ++i)
+                for (int which = 0; which < 2; ++which) {
+                    if (n == capacity) return VPP_OK;
+                    const int t = slot_tile(s, i, which);
+                    WorkItem w = {0, 0, 0, 0, 0, 0, 0};
+                    if (t >= 0) {
+                        w.row0 = s.row0 + t * bm;
+                        w.nrows = std::min(bm, s.len - t * bm);
+                        w.pos0 = s.prefix + t * bm;
+                        w.key_begin = r.begin;
+                        w.key_end = std::min(r.end, w.pos0 + w.nrows);
+                        w.split = r.b;
+                        w.kv_base = s.kv_start;
+                    }
+                    items[n++] = w;
+                }
+        }
+    } catch (const std::bad_alloc&) {
+        return VPP_ERR_NOMEM;
+    }
     return VPP_OK;
 }
 
@@ -1609,10 +1746,10 @@ struct RopeK {
     int64_t kr_st;
 };
 
-// How run_impl puts the work list into the workspace: through the plan's pinned
-// staging ring (asynchronous), or straight from the plan's host copy, which
-// allocates nothing (the copy out of host memory completes before the call
-// returns).
+// How run_impl puts a launch table too large for the kernel arguments into the
+// workspace: through the plan's pinned staging ring (asynchronous), or straight
+// from the plan's host memory, which allocates nothing (the copy out of memory
+// that is not pinned completes before the call returns).
 enum class Upload { staged, direct };
 
 vpp_status_t run_impl(vpp_chunk_attn_plan_t p, const void* q, int64_t q_st, int64_t q_sh, const void* k,
@@ -1643,16 +1780,18 @@ vpp_status_t run_impl(vpp_chunk_attn_plan_t p, const void* q, int64_t q_st, int6
     }
     if (!workspace || ((uintptr_t)workspace & 255u) != 0) return VPP_ERR_WORKSPACE;
     if (workspace_bytes < p->ws_bytes) return VPP_ERR_WORKSPACE;
-    if (p->items.empty()) return VPP_OK;  // nothing to do: every segment is empty
+    if (p->groups.empty()) return VPP_OK;  // nothing to do: every segment is empty
 
     hipStream_t stream = (hipStream_t)stream_ptr;
     char* ws = (char*)workspace;
-    if (upload == Upload::direct) {
-        // the paged path rewrites kv_base in its copy of the list; it always stages
-        if (pg) return VPP_ERR_INVALID_ARG;
-        if (hipMemcpyAsync(ws, p->items.data(), p->items_bytes, hipMemcpyHostToDevice, stream) != hipSuccess)
+    const size_t groups_bytes = p->groups.size() * sizeof(LaunchGroup);
+    const size_t merges_bytes = p->merges.size() * sizeof(CombineSeg);
+    if (p->table_bytes && upload == Upload::direct) {
+        if (hipMemcpyAsync(ws, p->groups.data(), groups_bytes, hipMemcpyHostToDevice, stream) != hipSuccess ||
+            (merges_bytes && hipMemcpyAsync(ws + groups_bytes, p->merges.data(), merges_bytes, hipMemcpyHostToDevice,
+                                            stream) != hipSuccess))
             return VPP_ERR_HIP;
-    } else {
+    } else if (p->table_bytes) {
         const int slot = p->next_slot;
         p->next_slot = (p->next_slot + 1) % STAGING_SLOTS;
         if (!p->staging_done[slot]) {
@@ -1663,44 +1802,44 @@ vpp_status_t run_impl(vpp_chunk_attn_plan_t p, const void* q, int64_t q_st, int6
             if (hipEventSynchronize(p->staging_done[slot]) != hipSuccess) return VPP_ERR_HIP;
             p->staging_pending[slot] = false;
         }
-        if (p->staging_cap[slot] < p->items_bytes) {
+        if (p->staging_cap[slot] < p->table_bytes) {
             if (p->staging[slot]) (void)hipHostFree(p->staging[slot]);
             p->staging[slot] = nullptr;
             p->staging_cap[slot] = 0;
-            if (hipHostMalloc((void**)&p->staging[slot], p->items_bytes, hipHostMallocDefault) != hipSuccess)
+            if (hipHostMalloc((void**)&p->staging[slot], p->table_bytes, hipHostMallocDefault) != hipSuccess)
                 return VPP_ERR_HIP;
-            p->staging_cap[slot] = p->items_bytes;
+            p->staging_cap[slot] = p->table_bytes;
         }
-        memcpy(p->staging[slot], p->items.data(), p->items_bytes);
-        if (pg) {
-            // paged: the kernel finds the segment's block-table row from kv_base
-            for (size_t i = 0; i < p->items.size(); ++i)
-                p->staging[slot][i].kv_base = ((int64_t)p->item_seg[i] << 32) | p->items[i].kv_base;
-        }
-        if (hipMemcpyAsync(ws, p->staging[slot], p->items_bytes, hipMemcpyHostToDevice, stream) != hipSuccess)
+        memcpy(p->staging[slot], p->groups.data(), groups_bytes);
+        if (merges_bytes) memcpy(p->staging[slot] + groups_bytes, p->merges.data(), merges_bytes);
+        if (hipMemcpyAsync(ws, p->staging[slot], p->table_bytes, hipMemcpyHostToDevice, stream) != hipSuccess)
             return VPP_ERR_HIP;
         if (hipEventRecord(p->staging_done[slot], stream) != hipSuccess) return VPP_ERR_HIP;
         p->staging_pending[slot] = true;
     }
 
     const vpp_chunk_attn_config_t& c = p->cfg;
-    AttnArgs a;
-    memset(&a, 0, sizeof a);
-    a.items = (const WorkItem*)ws;
+    Launch l;
+    memset(&l, 0, sizeof l);
+    l.nb = p->nb;
+    l.dqk = c.head_dim_qk;
+    l.workgroups = p->workgroups;
+    AttnArgs& a = l.a;
+    a.num_groups = (int32_t)p->groups.size();
+    if (p->table_bytes) a.groups = (const LaunchGroup*)ws;
+    else memcpy(l.groups.g, p->groups.data(), groups_bytes);
     a.q = (const u16*)q;
     a.k = (const u16*)k;
     a.v = (const u16*)v;
-    a.out = out;
+    a.out = (u16*)out;
     a.lse = lse;
+    a.part_o = (float*)(ws + p->part_o_off);
+    a.part_lse = (float*)(ws + p->part_lse_off);
     a.q_st = (int32_t)q_st; a.q_sh = (int32_t)q_sh; a.k_st = (int32_t)k_st; a.k_sh = (int32_t)k_sh;
     a.v_st = (int32_t)v_st; a.v_sh = (int32_t)v_sh; a.o_st = (int32_t)o_st; a.o_sh = (int32_t)o_sh;
     a.lse_sh = (int32_t)lse_sh;
-    // one workgroup per slot and head: the kernel reads entries 2*slot and 2*slot + 1
-    a.num_slots = p->num_slots;
-    a.num_entries = (int32_t)p->items.size();
     a.num_heads = c.num_q_heads;
     a.group = c.num_q_heads / c.num_kv_heads;
-    a.tokens = p->tokens;
     a.scale_log2 = (float)((double)p->scale * 1.4426950408889634);
     a.xcd_remap = env_xcd_remap();
     if (rope) {
@@ -1715,26 +1854,22 @@ vpp_status_t run_impl(vpp_chunk_attn_plan_t p, const void* q, int64_t q_st, int6
         a.page_shift = pg->page_shift;
         a.num_pages = pg->num_pages;
     }
-    const bool split = p->num_splits > 1;
-    CombineArgs ca;
-    memset(&ca, 0, sizeof ca);
-    if (split) {
-        size_t off = align256(p->items_bytes);
-        ca.part_o = (float*)(ws + off);
-        off += align256((size_t)p->num_splits * p->tokens * c.num_q_heads * c.head_dim_v * sizeof(float));
-        ca.part_lse = (float*)(ws + off);
-        a.out = (void*)ca.part_o;
-        a.lse = (float*)ca.part_lse;
-        ca.out = (u16*)out;
-        ca.lse = lse;
-        ca.o_st = o_st; ca.o_sh = o_sh; ca.lse_sh = lse_sh;
-        ca.tokens = p->tokens;
-        ca.num_heads = c.num_q_heads;
-        ca.splits = p->num_splits;
+    if (!p->merges.empty()) {
+        CombineArgs& m = l.merge;
+        m.num_segs = (int32_t)p->merges.size();
+        if (p->table_bytes) m.segs = (const CombineSeg*)(ws + groups_bytes);
+        else memcpy(l.segs.s, p->merges.data(), merges_bytes);
+        m.part_o = a.part_o;
+        m.part_lse = a.part_lse;
+        m.out = (u16*)out;
+        m.lse = lse;
+        m.o_st = o_st; m.o_sh = o_sh; m.lse_sh = lse_sh;
+        m.num_heads = c.num_q_heads;
+        m.blocks = p->merge_blocks;
     }
-    const hipError_t e = rope ? vpp_detail::launch_attn_rope(p->nb, a, split, ca, stream)
-                         : pg ? vpp_detail::launch_attn_paged(p->nb, c.head_dim_qk, a, split, ca, stream)
-                              : vpp_detail::launch_attn_contig(p->nb, c.head_dim_qk, a, split, ca, stream);
+    const hipError_t e = rope ? vpp_detail::launch_attn_rope(l, stream)
+                         : pg ? vpp_detail::launch_attn_paged(l, stream)
+                              : vpp_detail::launch_attn_contig(l, stream);
     return e == hipSuccess ? VPP_OK : VPP_ERR_HIP;
 }
 
@@ -1819,9 +1954,8 @@ extern "C" vpp_status_t vpp_chunk_attn_run_paged(vpp_chunk_attn_plan_t p, const 
     if (!stride_ok(k_sp) || !stride_ok(v_sp) || k_sp < 1 || v_sp < 1) return VPP_ERR_INVALID_ARG;
     if ((int64_t)page_size * k_st >= ((int64_t)1 << 31) || (int64_t)page_size * v_st >= ((int64_t)1 << 31))
         return VPP_ERR_INVALID_ARG;
-    for (size_t i = 0; i < p->items.size(); ++i)
-        if (p->items[i].kv_base % BN != 0 || p->items[i].kv_base >= ((int64_t)1 << 31))
-            return VPP_ERR_INVALID_ARG;  // a key tile must not straddle two pages
+    for (const SegPlan& s : p->segs)
+        if (s.kv_start % BN != 0) return VPP_ERR_INVALID_ARG;  // a key tile must not straddle two pages
     int shift = 0;
     while ((1 << shift) < page_size) ++shift;
     PagedKV pg{block_table, bt_st, k_sp, v_sp, shift, num_pages};

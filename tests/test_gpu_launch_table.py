@@ -1,0 +1,62 @@
+"""Chunks of many segments: the launch table around its limits, against the fp64 oracle.
+
+A run's launch table has one entry per segment and split piece that has keys. Up to 64
+entries travel in the kernel arguments, more are copied to the workspace; a workgroup finds
+its entry by comparing 64 at a time, so 64/65 and 4096/4097 are where the search takes
+another step. Segments without a prefix have one piece whatever the split count and write
+their results directly, next to split segments whose partials are merged.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import parity as PA
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+def _rand(shape, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return (torch.randn(shape, generator=g, device=DEV) / 8.0).to(torch.bfloat16)
+
+
+# (segments, rows of every second segment, prefix of every third, heads, split request)
+@pytest.mark.parametrize("nseg,rows,prefix,heads,splits", [
+    (64, 3, 0, (4, 2), 1),
+    (65, 3, 0, (4, 2), 1),
+    (33, 5, 130, (3, 1), 2),     # 44 pieces of 33 segments
+    (60, 2, 200, (4, 4), 3),     # 100 pieces, 20 merged segments
+    (200, 1, 140, (2, 1), 2),    # 267 pieces, 67 merged segments
+    (4096, 1, 0, (1, 1), 1),
+    (4097, 1, 0, (2, 1), 1),
+    (3, 300, 700, (4, 2), -1),
+])
+def test_many_segments(nseg, rows, prefix, heads, splits):
+    from paper_2608_26523_amd.attention import ChunkAttention
+    hq, hkv = heads
+    lens = [rows if i % 2 else 1 for i in range(nseg)]
+    pre = [prefix if i % 3 == 0 else 0 for i in range(nseg)]
+    kvs, at = [], 0
+    for n, p in zip(lens, pre):
+        kvs.append(at)
+        at += n + p
+    cu = np.cumsum([0] + lens)
+    tok = int(cu[-1])
+    print("case:", nseg, rows, prefix, heads, splits, flush=True)
+    q, k, v = _rand((tok, hq, 64), 1), _rand((at, hkv, 64), 2), _rand((at, hkv, 64), 3)
+    attn = ChunkAttention(hq, hkv, 64, 64, max_chunk_tokens=tok, max_kv_len=at, max_segments=nseg,
+                          num_splits=splits)
+    out, lse = PA.run_chunk(attn, q, k, v, cu, kvs, pre)
+    ro, rl = oracle.attention_full(q.cpu(), k.cpu(), v.cpu(), cu, kvs, pre)
+    r, h = np.repeat(np.arange(tok), hq), np.tile(np.arange(hq), tok)
+    rep = PA.compare(out, lse, r, h, ro.reshape(tok * hq, -1), rl.T.reshape(-1))
+    assert rep.ok(), str(rep)
+    # the entry point without a workspace, whose table copy is synchronous
+    out2, lse2 = torch.full_like(out, -3.0), torch.full_like(lse, -3.0)
+    attn.run_noalloc(q, k, v, out2, lse2)
+    torch.cuda.synchronize()
+    assert torch.equal(out, out2) and torch.equal(lse, lse2)
