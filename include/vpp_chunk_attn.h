@@ -265,15 +265,17 @@ const char* vpp_status_str(vpp_status_t status);
 
 /* Summary of a plan, for callers that size buffers or report work. */
 typedef struct {
-    int32_t num_tiles;        /* query tiles (per head) in the chunk               */
+    int32_t num_tiles;        /* query tiles (per head group) in the chunk         */
     int32_t num_splits;       /* split count chosen (1 = no merge pass)            */
     int32_t num_work_items;   /* work-list entries: two per slot                   */
-    int32_t block_m;          /* query rows per tile                               */
+    int32_t block_m;          /* rows per tile: (token, head) pairs of the heads
+                                 that share it, the largest divisor of Hq/Hkv up
+                                 to 16                                             */
     int32_t block_n;          /* keys per inner step                               */
     int32_t num_tokens;       /* cu_q[n]                                           */
     int64_t workspace_bytes;  /* same value vpp_chunk_attn_plan returned           */
     double pairs;             /* visible (query, key) pairs per head               */
-    int32_t num_slots;        /* work slots = workgroups per head of the launch    */
+    int32_t num_slots;        /* work slots = workgroups per head group            */
 } vpp_chunk_attn_plan_info_t;
 
 vpp_status_t vpp_chunk_attn_plan_info(vpp_chunk_attn_plan_t plan,
@@ -283,7 +285,7 @@ vpp_status_t vpp_chunk_attn_plan_info(vpp_chunk_attn_plan_t plan,
  * coordinates). */
 typedef struct {
     int32_t row0;      /* first chunk row of the tile                         */
-    int32_t nrows;     /* rows in the tile (1 .. block_m)                      */
+    int32_t nrows;     /* chunk rows in the tile (1 .. block_m / heads a tile) */
     int32_t pos0;      /* in-request position of row0                          */
     int32_t key_begin; /* keys [key_begin, key_end) of the request             */
     int32_t key_end;
@@ -293,7 +295,7 @@ typedef struct {
 
 /* Copy up to `capacity` work items of the plan, in launch order; *count gets
  * the plan's item count. Entries 2m and 2m+1 form work slot m, which one
- * workgroup per head runs: the first entry's tile with its keys ascending, then
+ * workgroup per head group runs: the first entry's tile with its keys ascending, then
  * the second's (the partner tile from the other end of the same segment, in the
  * same split piece) with its keys descending. A second entry with nrows = 0 is
  * empty. Every (tile, split piece) appears exactly once; a piece without keys

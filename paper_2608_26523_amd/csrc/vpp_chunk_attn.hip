@@ -137,10 +137,11 @@ struct LaunchGroup {
     int32_t key_end;    // (INT32_MAX) runs on to each tile's own end
     int32_t seg;        // block-table row (paged cache)
     int32_t part0;      // first row of the piece's fp32 partials; < 0: final results
-    int32_t slots;      // work slots per head: two tiles each, or one when slots == tiles
+    int32_t slots;      // work slots per head group: two tiles each, or one when slots == tiles
+    int32_t tiles;      // query tiles per head group
 };
 // A chunk of up to INLINE_GROUPS groups (16 segments with 4 pieces each, or any
-// one segment) carries its table in the kernel arguments: the 2.5 KB travel with
+// one segment) carries its table in the kernel arguments: the 2.8 KB travel with
 // the dispatch packet, where an upload of its own costs a copy of 2 us and the
 // gaps around it, 12 to 15 us a run. Kernel arguments end at 4 KB.
 constexpr int INLINE_GROUPS = 64;
@@ -162,6 +163,12 @@ struct AttnArgs {
     // element strides (the host checks that they fit in 31 bits)
     int32_t q_st, q_sh, k_st, k_sh, v_st, v_sh, o_st, o_sh, lse_sh;
     int32_t group;     // Hq / Hkv
+    // Query heads per tile. A tile's row r is token r / pack of the tile, head
+    // r % pack of `pack` heads that read the same kv head; r / pack is
+    // (r * pack_magic) >> 16.
+    int32_t pack, pack_magic;
+    int32_t tile_tokens;  // tokens per tile
+    int32_t head_groups;  // Hq / pack
     float scale_log2;  // softmax scale * log2(e)
     int32_t xcd_remap;
     // Paged cache (PAGED kernels only). Cache row j of segment s is row
@@ -610,7 +617,6 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
     char* const kbuf0 = smem;
     char* const vbuf0 = smem + 2 * T::K_BYTES;
 
-    constexpr int BM = block_rows(NB);
     // this workgroup's launch group; the inline table follows the first argument
     auto group_base = [](const LaunchGroup* table) {
         return table ? (uint64_t)(uintptr_t)table
@@ -620,18 +626,20 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
     const_group_t* const grp = const_ptr<const_group_t>(group_base(a.groups)) + gidx;
     const int slots = grp->slots;
     int slot, h;
-    work_coords((int)blockIdx.x - grp->wg0, slots, a.num_heads, a.xcd_remap != 0, slot, h);
-    const int seg_tiles = (grp->len + BM - 1) / BM;
+    work_coords((int)blockIdx.x - grp->wg0, slots, a.head_groups, a.xcd_remap != 0, slot, h);
+    h *= a.pack;  // the tile's first head
+    const int seg_tiles = grp->tiles;
+    auto row_token = [](int r, int magic) { return (int)((uint32_t)r * (uint32_t)magic >> 16); };
     // A slot holds up to two tiles of the segment: the first runs its key range
     // ascending, its partner from the other end (if any) descending.
 #pragma nounroll
     for (int sub = 0; sub < 2; ++sub) {
         const int ti = sub == 0 ? slot : seg_tiles - 1 - slot;
         if (sub == 1 && (slots == seg_tiles || ti == slot)) break;
-        const int t_row0 = ti * BM;  // the tile's first row in the segment
+        const int t_row0 = ti * a.tile_tokens;  // the tile's first token in the segment
         struct { int row0, nrows, pos0, key_begin, key_end; } it;
         it.row0 = grp->row0 + t_row0;
-        it.nrows = min(BM, grp->len - t_row0);
+        it.nrows = min(a.tile_tokens, grp->len - t_row0);
         it.pos0 = grp->prefix + t_row0;
         it.key_begin = grp->key_begin;
         it.key_end = min(grp->key_end, it.pos0 + it.nrows);
@@ -679,19 +687,22 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
         // This lane's NB query rows (one per 32-column block of S^T), as B
         // operands in AGPRs. Rows past the tile re-read its last row (their results
         // are never stored), so every load stays inside q.
+        const int tile_rows = it.nrows * a.pack;  // at most BM
         bf16x8 qf[NB][KS];
         int qlim[NB];   // last key position the row may see, minus lg*4 (see masking)
         bool qvalid[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const int rloc = wave * WROWS + nb * 32 + lr;
-            qvalid[nb] = rloc < it.nrows;
-            qlim[nb] = min(it.pos0 + rloc, ke - 1) - lg * 4;
-            const u16* qp = a.q + (int64_t)(it.row0 + min(rloc, it.nrows - 1)) * a.q_st + (int64_t)h * a.q_sh + lg * 8;
+            qvalid[nb] = rloc < tile_rows;
+            const int r = min(rloc, tile_rows - 1);
+            const int tok = row_token(r, a.pack_magic);
+            qlim[nb] = min(it.pos0 + tok, ke - 1) - lg * 4;
+            const u16* qp = a.q + (int64_t)(it.row0 + tok) * a.q_st + (int64_t)(h + r - tok * a.pack) * a.q_sh + lg * 8;
             load_q_agpr<KS>(qf[nb], qp);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        const int wave_first = it.pos0 + wave * WROWS;
+        const int wave_first = it.pos0 + row_token(wave * WROWS, a.pack_magic);
 
         // Global->LDS copy of one tile through a buffer resource whose base is the
         // tile's first key row and whose size ends at the last key of the range:
@@ -1131,9 +1142,11 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
             const float inv_l = l_tot > 0.f ? 1.f / l_tot : 0.f;
             const float lse_val = l_tot > 0.f ? (m_run[nb] + __log2f(l_tot)) * 0.69314718055994531f : -INFINITY;
             if (!qvalid[nb]) continue;
-            const int row = row0 + wave * WROWS + nb * 32 + lr;
+            const int rloc = wave * WROWS + nb * 32 + lr;
+            const int tok = row_token(rloc, ka->pack_magic);
+            const int row = row0 + tok, hh = h + rloc - tok * ka->pack;
             if (part0 >= 0) {
-                const int64_t prow = (int64_t)row * ka->num_heads + h;
+                const int64_t prow = (int64_t)row * ka->num_heads + hh;
                 float* po = ka->part_o + prow * DV;
 #pragma unroll
                 for (int d = 0; d < DB; ++d)
@@ -1145,7 +1158,7 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
                     }
                 if (lg == 0) ka->part_lse[prow] = lse_val;
             } else {
-                u16* op = ka->out + (int64_t)row * ka->o_st + (int64_t)h * ka->o_sh;
+                u16* op = ka->out + (int64_t)row * ka->o_st + (int64_t)hh * ka->o_sh;
 #pragma unroll
                 for (int d = 0; d < DB; ++d)
 #pragma unroll
@@ -1155,7 +1168,7 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
                         for (int j = 0; j < 4; ++j) w[j] = (__bf16)(o[d][nb][c * 4 + j] * inv_l);
                         *(bf16x4*)(op + d * 32 + c * 8 + lg * 4) = w;
                     }
-                if (lg == 0 && ka->lse) ka->lse[(int64_t)h * ka->lse_sh + row] = lse_val;
+                if (lg == 0 && ka->lse) ka->lse[(int64_t)hh * ka->lse_sh + row] = lse_val;
             }
         }
     }  // slot tiles
@@ -1316,6 +1329,7 @@ struct vpp_chunk_attn_plan_s {
     int32_t num_tiles = 0;
     int32_t num_splits = 1;
     int32_t nb = 2;  // 32-row query blocks per wave of the kernel variant the plan was made for
+    int32_t pack = 1, tile_tokens = 256;
     int32_t tokens = 0;
     double pairs = 0.0;
     size_t table_bytes = 0;  // groups, then merges, where they exceed the kernel arguments; else 0
@@ -1346,6 +1360,19 @@ int choose_nb(const vpp_chunk_attn_config_t& c, int64_t tiles256, double mean_ke
     if (e && (atoi(e) == 1 || atoi(e) == 2)) return atoi(e);
     if (c.head_dim_qk <= 128 && tiles256 * c.num_q_heads <= 2 * 256 && mean_keys256 <= 8192.0) return 1;
     return 2;
+}
+
+// Query heads per tile: the largest divisor of Hq/Hkv up to 16. The heads that
+// share a kv head read the same keys, so a tile of 256 rows may hold 16 tokens of 16
+// of them as well as 256 tokens of one. It then wastes less: a short segment fills
+// its tiles (43 rows of 64/4 heads: 3 tiles a kv head instead of 16), and a causal
+// tile reaches 16 keys past its first token's instead of 256. One tile serves the
+// heads that would each read its keys through the L2 again.
+int heads_per_tile(const vpp_chunk_attn_config_t& c) {
+    const int g = c.num_q_heads / c.num_kv_heads;
+    for (int n = std::min(g, 16); n > 1; --n)
+        if (g % n == 0) return n;
+    return 1;
 }
 
 vpp_status_t check_config(const vpp_chunk_attn_config_t& c) {
@@ -1439,18 +1466,18 @@ std::vector<PieceRef> launch_order(const std::vector<SegPlan>& segs, int n, int 
 // its pieces write and the merge reads back. The unsplit plan is kept whenever its
 // simulated makespan is within 5 % of the ideal (total work spread evenly), which
 // covers every chunk with enough even slots.
-int auto_split(const vpp_chunk_attn_config_t& c, int bm, int wg_per_cu, int64_t max_prefix, int32_t tokens,
+int auto_split(const vpp_chunk_attn_config_t& c, int nb, int pack, int tt, int64_t max_prefix, int32_t tokens,
                std::vector<SegPlan>& segs) {
     constexpr int NXCD = 8, CU_PER_XCD = 32;
     constexpr double TILE_OVERHEAD = 2.0;  // fixed cost of a tile, in key tiles
-    const int heads = c.num_q_heads;
-    // one key tile of one workgroup: 2 bm BN (dqk + dv) flop at ~5 TFLOP/s per CU
-    const double tile_s = 2.0 * bm * BN * (c.head_dim_qk + c.head_dim_v) / 5.0e12;
+    const int heads = c.num_q_heads / pack, wg_per_cu = nb == 1 ? 2 : 1;
+    // one key tile of one workgroup: 2 rows BN (dqk + dv) flop at ~5 TFLOP/s per CU
+    const double tile_s = 2.0 * block_rows(nb) * BN * (c.head_dim_qk + c.head_dim_v) / 5.0e12;
     auto entry_cost = [](int64_t keys) { return keys > 0 ? (double)((keys + BN - 1) / BN) + TILE_OVERHEAD : 0.0; };
     // simulated seconds of the launch, and of its work spread evenly over the chip
     auto simulate = [&](int n, double& ideal) {
         for (SegPlan& s : segs) s.pieces = n;
-        const std::vector<PieceRef> order = launch_order(segs, n, bm, false);
+        const std::vector<PieceRef> order = launch_order(segs, n, tt, false);
         const int lanes = CU_PER_XCD * wg_per_cu;
         std::vector<std::vector<double>> costs;
         double total = 0.0;
@@ -1459,9 +1486,9 @@ int auto_split(const vpp_chunk_attn_config_t& c, int bm, int wg_per_cu, int64_t 
             const SegPlan& s = segs[(size_t)r.si];
             std::vector<double> v((size_t)s.slots());
             for (int i = 0; i < s.slots(); ++i) {
-                v[(size_t)i] = entry_cost(tile_keys(s, bm, i, r.begin, r.end));
+                v[(size_t)i] = entry_cost(tile_keys(s, tt, i, r.begin, r.end));
                 const int t = slot_tile(s, i, 1);
-                if (t >= 0) v[(size_t)i] += entry_cost(tile_keys(s, bm, t, r.begin, r.end));
+                if (t >= 0) v[(size_t)i] += entry_cost(tile_keys(s, tt, t, r.begin, r.end));
                 total += v[(size_t)i] * heads;
             }
             even = even && (int64_t)s.slots() * heads % NXCD == 0;
@@ -1496,7 +1523,7 @@ int auto_split(const vpp_chunk_attn_config_t& c, int bm, int wg_per_cu, int64_t 
     // partial bytes per piece: fp32 out and lse of every (row, head), written once and
     // read once, at the ~3 TB/s the split chunks of the mixed workload were measured to
     // pay; a split must also be predicted to gain at least 3 %
-    const double partial_s = 2.0 * tokens * heads * (4.0 * c.head_dim_v + 4.0) / 3.0e12;
+    const double partial_s = 2.0 * tokens * c.num_q_heads * (4.0 * c.head_dim_v + 4.0) / 3.0e12;
     int best = 1;
     double best_t = 0.97 * t1;
     static const int candidates[] = {2, 3, 4, 6, 8, 12, 16};
@@ -1551,7 +1578,8 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
             keys256 += (double)prefix_len[s] + (r0 - cu_q[s]) + std::min(block_rows(2), cu_q[s + 1] - r0);
         }
     const int nb = choose_nb(c, tiles256, tiles256 ? keys256 / tiles256 : 0.0);
-    const int BM = block_rows(nb);
+    const int pack = heads_per_tile(c);
+    const int tt = block_rows(nb) / pack;  // tokens per tile
     // Work slots. A workgroup runs one slot: up to two query tiles of one segment,
     // tile i with its key range ascending, then tile T-1-i (the partner from the
     // other end of the segment) descending. A pair's two ranges together span the
@@ -1571,17 +1599,23 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
         for (int s = 0; s < num_segments; ++s) {
             const int32_t len = cu_q[s + 1] - cu_q[s];
             if (len == 0) continue;
-            SegPlan sp{s, cu_q[s], len, (int32_t)prefix_len[s], (int32_t)kv_start[s], (int32_t)(((int64_t)len + BM - 1) / BM), 1, true};
+            SegPlan sp{s, cu_q[s], len, (int32_t)prefix_len[s], (int32_t)kv_start[s], 
+                       (int32_t)(((int64_t)len + tt - 1) / tt), 1, true};
             // visible pairs: sum over rows of (position + 1)
             pairs += (double)len * (double)prefix_len[s] + 0.5 * (double)len * (len + 1.0);
             ntiles += sp.tiles;
-            nslots += sp.slots();
             max_prefix = std::max(max_prefix, prefix_len[s]);
             segs.push_back(sp);
         }
+        // a pair of tiles shares reads only where the chip is full: with fewer tiles
+        // than workgroups fit, each runs alone and finishes in half the time
+        for (SegPlan& s : segs) {
+            s.paired = ntiles * (c.num_q_heads / pack) > 256 * (3 - nb);
+            nslots += s.slots();
+        }
         if (!segs.empty())
             nsplit = c.num_splits >= 1 ? fixed_splits(c, max_prefix)
-                                       : auto_split(c, BM, nb == 1 ? 2 : 1, max_prefix, cu_q[num_segments], segs);
+                                       : auto_split(c, nb, pack, tt, max_prefix, cu_q[num_segments], segs);
         for (SegPlan& s : segs) s.pieces = nsplit;
 
         // partial rows of the split segments, piece by piece; a segment with one piece
@@ -1600,15 +1634,15 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
             part_rows += (int64_t)pieces * segs[k].len;
             blocks += ((int64_t)segs[k].len * c.num_q_heads * (c.head_dim_v / 4) + 255) / 256;
         }
-        for (const PieceRef& r : launch_order(segs, nsplit, BM, false)) {
+        for (const PieceRef& r : launch_order(segs, nsplit, tt, false)) {
             const SegPlan& s = segs[(size_t)r.si];
-            LaunchGroup g{(int32_t)wgs, s.row0, s.len, s.prefix, s.kv_start, r.begin, r.end, s.seg, -1, s.slots()};
+            LaunchGroup g{(int32_t)wgs, s.row0, s.len, s.prefix, s.kv_start, r.begin, r.end, s.seg, -1, s.slots(), s.tiles};
             if (next_part[(size_t)r.si] >= 0) {
                 g.part0 = next_part[(size_t)r.si];
                 next_part[(size_t)r.si] += s.len;
             }
             groups.push_back(g);
-            wgs += (int64_t)g.slots * c.num_q_heads;
+            wgs += (int64_t)g.slots * (c.num_q_heads / pack);
         }
     } catch (const std::bad_alloc&) {
         return VPP_ERR_NOMEM;
@@ -1621,6 +1655,8 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
         *inout_plan = p;
     }
     p->nb = nb;
+    p->pack = pack;
+    p->tile_tokens = tt;
     p->scale = c.softmax_scale > 0.f ? c.softmax_scale : (float)(1.0 / sqrt((double)c.head_dim_qk));
     p->segs.swap(segs);
     p->groups.swap(groups);
@@ -1664,7 +1700,7 @@ extern "C" vpp_status_t vpp_chunk_attn_plan_items(vpp_chunk_attn_plan_t p, vpp_c
     if (!p || !count || capacity < 0 || (capacity > 0 && !items)) return VPP_ERR_INVALID_ARG;
     *count = (int32_t)p->num_items;
     if (capacity == 0) return VPP_OK;
-    const int bm = block_rows(p->nb);
+    const int bm = p->tile_tokens;
     int32_t n = 0;
     try {
         for (const PieceRef& r : launch_order(p->segs, p->num_splits, bm, true)) {
@@ -1840,6 +1876,10 @@ vpp_status_t run_impl(vpp_chunk_attn_plan_t p, const void* q, int64_t q_st, int6
     a.lse_sh = (int32_t)lse_sh;
     a.num_heads = c.num_q_heads;
     a.group = c.num_q_heads / c.num_kv_heads;
+    a.pack = p->pack;
+    a.pack_magic = (65536 + p->pack - 1) / p->pack;  // exact for r < 256, pack <= 16
+    a.tile_tokens = p->tile_tokens;
+    a.head_groups = c.num_q_heads / p->pack;
     a.scale_log2 = (float)((double)p->scale * 1.4426950408889634);
     a.xcd_remap = env_xcd_remap();
     if (rope) {
