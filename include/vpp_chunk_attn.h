@@ -77,7 +77,8 @@ typedef struct {
     int32_t max_segments;     /* bound on the number of segments                  */
     int64_t max_kv_len;       /* bound on kv_start + prefix_len + len (cache rows) */
     int32_t num_splits;       /* split of the key range with an lse merge:
-                                 -1 automatic, 1 off, 2..16 fixed                  */
+                                 -1 automatic (each segment its own count, up to
+                                 64), 1 off, 2..16 fixed                           */
 } vpp_chunk_attn_config_t;
 
 typedef struct vpp_chunk_attn_plan_s* vpp_chunk_attn_plan_t;
@@ -94,7 +95,7 @@ typedef struct vpp_chunk_attn_plan_s* vpp_chunk_attn_plan_t;
  * *inout_plan == NULL creates a plan (owned by the library until
  * vpp_chunk_attn_destroy); a non-NULL plan is refilled in place with the same
  * config (cfg may be NULL then). Refilling never blocks: a run hands its launch
- * table (one entry per segment and split piece) to the kernel in the kernel
+ * table (one entry per segment) to the kernel in the kernel
  * arguments, or, past 64 entries, copies it to the device from a pinned staging
  * slot of its own (a ring of 4 per plan); only a run that reuses a slot whose
  * earlier copy is still in flight waits, on the host, for that copy.
@@ -109,8 +110,7 @@ vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg,
 
 /*
  * Run a planned chunk, asynchronously on `stream` (a hipStream_t; NULL is the
- * default stream). Enqueues, in order: for plans of more than 64 segments and
- * split pieces the copy of the launch table into the workspace, the attention
+ * default stream). Enqueues, in order: for plans of more than 64 segments the copy of the launch table into the workspace, the attention
  * kernel, and -- when the plan splits a segment's key range -- the merge kernel. Never synchronizes the stream. All pointers are
  * caller-owned device memory that must stay valid until the stream reaches the
  * end of this work; lse may be NULL. The workspace (>= the planned bytes,
@@ -266,7 +266,7 @@ const char* vpp_status_str(vpp_status_t status);
 /* Summary of a plan, for callers that size buffers or report work. */
 typedef struct {
     int32_t num_tiles;        /* query tiles (per head group) in the chunk         */
-    int32_t num_splits;       /* split count chosen (1 = no merge pass)            */
+    int32_t num_splits;       /* most pieces a segment is cut into (1 = no merge)  */
     int32_t num_work_items;   /* work-list entries: two per slot                   */
     int32_t block_m;          /* rows per tile: (token, head) pairs of the heads
                                  that share it, the largest divisor of Hq/Hkv up
@@ -299,7 +299,8 @@ typedef struct {
  * the second's (the partner tile from the other end of the same segment, in the
  * same split piece) with its keys descending. A second entry with nrows = 0 is
  * empty. Every (tile, split piece) appears exactly once; a piece without keys
- * (key_begin == key_end) is not launched. */
+ * (key_begin == key_end) is not launched. A slot may hold one tile (its second
+ * entry empty) or two, as the plan finds faster. */
 vpp_status_t vpp_chunk_attn_plan_items(vpp_chunk_attn_plan_t plan,
                                        vpp_chunk_attn_work_item_t* items,
                                        int32_t capacity, int32_t* count);

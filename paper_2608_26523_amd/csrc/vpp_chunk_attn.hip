@@ -54,7 +54,7 @@ constexpr int NWAVES = 4;
 constexpr int block_rows(int nb) { return 32 * nb * NWAVES; }
 [[maybe_unused]] constexpr int BM_MAX = block_rows(2);
 constexpr int NTHREADS = 64 * NWAVES;
-constexpr int MAX_SPLITS = 16;
+[[maybe_unused]] constexpr int MAX_SPLITS = 16;  // a fixed split request
 [[maybe_unused]] constexpr int STAGING_SLOTS = 4;
 // cache layouts (kernel template argument KVM)
 [[maybe_unused]] constexpr int KV_CONTIG = 0, KV_PAGED = 1, KV_ROPE = 2;
@@ -121,29 +121,36 @@ static_assert(sizeof(WorkItem) == 32, "work item layout");
 
 }  // namespace
 
+namespace {
+// First key of piece b of a p-key prefix cut into n tile-aligned pieces; the last
+// piece runs on to each tile's own end (its keys within the chunk).
+__host__ __device__ inline int32_t piece_begin(int32_t p, int n, int b) {
+    return (int32_t)((uint32_t)(p / BN) * (uint32_t)b / (uint32_t)n * (uint32_t)BN);
+}
+}  // namespace
+
 // Kernel argument blocks, shared by the translation units that instantiate
 // the kernels (the build compiles this file once per part, in parallel).
 namespace vpp_detail {
 
-// One launch group: the workgroups of one split piece of one segment, all heads
-// and work slots. Groups are contiguous runs of the grid, longest first.
+// One launch group: the workgroups of one segment, all heads, split pieces and
+// work slots. Groups are contiguous runs of the grid, longest slots first.
 struct LaunchGroup {
     int32_t wg0;        // the group's first workgroup
     int32_t row0;       // first chunk row of the segment
     int32_t len;        // rows of the segment
     int32_t prefix;     // in-request position of the first row
     int32_t kv_start;   // cache row of the request's position 0
-    int32_t key_begin;  // keys [key_begin, key_end) of the request; the last piece
-    int32_t key_end;    // (INT32_MAX) runs on to each tile's own end
     int32_t seg;        // block-table row (paged cache)
-    int32_t part0;      // first row of the piece's fp32 partials; < 0: final results
-    int32_t slots;      // work slots per head group: two tiles each, or one when slots == tiles
+    int32_t pieces;     // split pieces of the prefix (piece_begin)
+    int32_t part0;      // first row of piece 0's fp32 partials; < 0: final results
+    int32_t slots;      // work slots per head group and piece: two tiles, or one when slots == tiles
     int32_t tiles;      // query tiles per head group
 };
-// A chunk of up to INLINE_GROUPS groups (16 segments with 4 pieces each, or any
-// one segment) carries its table in the kernel arguments: the 2.8 KB travel with
-// the dispatch packet, where an upload of its own costs a copy of 2 us and the
-// gaps around it, 12 to 15 us a run. Kernel arguments end at 4 KB.
+// A chunk of up to INLINE_GROUPS segments carries its table in the kernel
+// arguments: the 2.5 KB travel with the dispatch packet, where an upload of its own
+// costs a copy of 2 us and the gaps around it, 12 to 15 us a run. Kernel arguments
+// end at 4 KB.
 constexpr int INLINE_GROUPS = 64;
 struct GroupTable {
     LaunchGroup g[INLINE_GROUPS];
@@ -326,19 +333,26 @@ __device__ __forceinline__ int find_entry(uint64_t table, int stride, int n, int
     return __builtin_amdgcn_readfirstlane(lo);
 }
 
-// Workgroup i of a group -> (slot, head). Consecutive workgroups land on the 8
-// XCDs round robin; the remap gives each XCD a contiguous run of the group's
-// head-major order (the slots of the same heads, which read the same K/V through
-// that XCD's L2). Every group is spread over all XCDs, so a long group loads
-// them alike.
-__device__ __forceinline__ void work_coords(int i, int slots, int heads, bool remap, int& slot, int& head) {
-    if (remap) {
+// Workgroup i of a group -> (slot, head), `heads` counting split pieces too (the
+// pieces of a head follow each other). Consecutive workgroups land on the 8 XCDs
+// round robin. Slots of two tiles (paired) are alike: each XCD gets a contiguous run
+// of the group's head-major order, the slots of the same heads, which read the same
+// K/V through that XCD's L2. Slots of one tile grow with their index: the XCDs that
+// share a head take turns at its slots, longest first (contiguous runs gave one XCD
+// the short half and the next the long half of a causal segment: 1120 us where pairs
+// take 984, at 6915 rows and 64/4 heads). Every group is spread over all XCDs.
+__device__ __forceinline__ void work_coords(int i, int slots, int heads, bool paired, bool remap, int& slot, int& head) {
+    if (remap && paired) {
         const int n = slots * heads;
         const int x = i & 7;
         i = x * (n >> 3) + min(x, n & 7) + (i >> 3);
+    } else if (remap) {
+        const int g = min(8, heads & -heads);  // XCDs x and x + g share heads
+        i = (i & (g - 1)) * (heads / g) * slots + i / g;
     }
     head = i / slots;
     slot = i - head * slots;
+    if (!paired) slot = slots - 1 - slot;
 }
 
 template <int DQK, int DV, int NB>
@@ -624,25 +638,34 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
     };
     const int gidx = find_entry(group_base(a.groups), sizeof(LaunchGroup), a.num_groups, (int)blockIdx.x);
     const_group_t* const grp = const_ptr<const_group_t>(group_base(a.groups)) + gidx;
-    const int slots = grp->slots;
+    const int slots = grp->slots, pieces = grp->pieces;
     int slot, h;
-    work_coords((int)blockIdx.x - grp->wg0, slots, a.head_groups, a.xcd_remap != 0, slot, h);
-    h *= a.pack;  // the tile's first head
     const int seg_tiles = grp->tiles;
+    const bool paired = slots != seg_tiles;
+    work_coords((int)blockIdx.x - grp->wg0, slots, a.head_groups * pieces, paired, a.xcd_remap != 0, slot, h);
+    int piece = 0, piece_kb = 0, piece_ke = INT32_MAX;
+    if (pieces > 1) {
+        const int hg = h / pieces;
+        piece = pieces - 1 - (h - hg * pieces);  // the last piece is the longest: first
+        h = hg;
+        piece_kb = piece_begin(grp->prefix, pieces, piece);
+        if (piece + 1 < pieces) piece_ke = piece_begin(grp->prefix, pieces, piece + 1);
+    }
+    h *= a.pack;  // the tile's first head
     auto row_token = [](int r, int magic) { return (int)((uint32_t)r * (uint32_t)magic >> 16); };
     // A slot holds up to two tiles of the segment: the first runs its key range
     // ascending, its partner from the other end (if any) descending.
 #pragma nounroll
     for (int sub = 0; sub < 2; ++sub) {
         const int ti = sub == 0 ? slot : seg_tiles - 1 - slot;
-        if (sub == 1 && (slots == seg_tiles || ti == slot)) break;
+        if (sub == 1 && (!paired || ti == slot)) break;
         const int t_row0 = ti * a.tile_tokens;  // the tile's first token in the segment
         struct { int row0, nrows, pos0, key_begin, key_end; } it;
         it.row0 = grp->row0 + t_row0;
         it.nrows = min(a.tile_tokens, grp->len - t_row0);
         it.pos0 = grp->prefix + t_row0;
-        it.key_begin = grp->key_begin;
-        it.key_end = min(grp->key_end, it.pos0 + it.nrows);
+        it.key_begin = piece_kb;
+        it.key_end = min(piece_ke, it.pos0 + it.nrows);
         const int64_t kv_start = grp->kv_start;
         // every wave is done with the LDS tiles of the slot's previous tile before
         // this tile's first copies overwrite them
@@ -1135,7 +1158,7 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
         asm volatile("" : "+s"(ka));
         const_group_t* const g2 = const_ptr<const_group_t>(group_base(ka->groups)) + gidx;
         const int part0 = g2->part0;
-        const int row0 = (part0 >= 0 ? part0 : g2->row0) + t_row0;
+        const int row0 = (part0 >= 0 ? part0 + piece * g2->len : g2->row0) + t_row0;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const float l_tot = lane_swap32_add(l_part[nb]);
@@ -1175,39 +1198,89 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
 }
 
 
+// Lane groups that share the pieces of one (row, head) in the merge. Many pieces
+// mean few rows (a split is what fills the chip with them), and one group walking 37
+// pieces takes 14 us of load latency: up to eight take every eighth piece each.
+__host__ __device__ constexpr int merge_ways(int pieces) {
+    return pieces >= 16 ? 8 : pieces >= 8 ? 4 : pieces >= 4 ? 2 : 1;
+}
+
 // Merge of split partials: lse = log sum_b exp(lse_b); out = sum_b exp(lse_b - lse) O_b.
-// DV/4 threads per (row, head), 4 values each; a block stays within one segment.
+// DV/4 threads a lane group, 4 values each; a block stays within one segment.
 template <int DV>
 __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, CombineTable) {
-    constexpr int G = DV / 4;
+    constexpr int G = DV / 4, GROUPS = 256 / G;
     const uint64_t table = a.segs ? (uint64_t)(uintptr_t)a.segs
                                   : (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(CombineArgs);
     const_seg_t* const sg = const_ptr<const_seg_t>(table) +
                             find_entry(table, sizeof(CombineSeg), a.num_segs, (int)blockIdx.x);
     const int len = sg->len, n = sg->pieces;
-    const int64_t pair = ((int64_t)((int)blockIdx.x - sg->block0) * 256 + threadIdx.x) / G;
-    const int c = (int)(threadIdx.x % G);
-    if (pair >= (int64_t)len * a.num_heads) return;
-    const int row = (int)(pair / a.num_heads);
-    const int h = (int)(pair - (int64_t)row * a.num_heads);
-    const int64_t p0 = ((int64_t)sg->part0 + row) * a.num_heads + h;  // piece 0; pieces are `step` apart
-    const int64_t step = (int64_t)len * a.num_heads;
-    const float* const pl = a.part_lse + p0;
-    const float* const po = a.part_o + p0 * DV + c * 4;
-    float mx = -INFINITY;
-    for (int b = 0; b < n; ++b) mx = fmaxf(mx, pl[b * step]);
+    const int ways = merge_ways(n);
+    const int grp = threadIdx.x / G, c = threadIdx.x % G;
+    const int way = grp % ways;
+    const int64_t pairs = (int64_t)len * a.num_heads;
+    const int64_t pair = (int64_t)((int)blockIdx.x - sg->block0) * (GROUPS / ways) + grp / ways;
+    const bool valid = pair < pairs;
+    const int64_t at = valid ? pair : pairs - 1;  // spare groups repeat the last pair, and store nothing
+    const int row = (int)(at / a.num_heads);
+    const int h = (int)(at - (int64_t)row * a.num_heads);
+    // piece b of the pair: `pairs` entries further on
+    const float* const pl = a.part_lse + (int64_t)sg->part0 * a.num_heads + at;
+    const float* const po = a.part_o + ((int64_t)sg->part0 * a.num_heads + at) * DV + c * 4;
+    float mx = -INFINITY, den = 0.f;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    float den = 0.f;
-    for (int b = 0; b < n; ++b) {
-        const float l = pl[b * step];
-        const float w = (l == -INFINITY) ? 0.f : __expf(l - mx);
-        den += w;
-        const float4 v = *(const float4*)(po + b * step * DV);
-        acc[0] += w * v.x;
-        acc[1] += w * v.y;
-        acc[2] += w * v.z;
-        acc[3] += w * v.w;
+    for (int b0 = way; b0 < n; b0 += 4 * ways) {
+        float l[4];
+        float4 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {  // four pieces in flight; past the last one: weight 0
+            const int b = b0 + j * ways;
+            const int64_t off = (int64_t)(b < n ? b : b0) * pairs;
+            l[j] = b < n ? pl[off] : -INFINITY;
+            v[j] = *(const float4*)(po + off * DV);
+        }
+        const float m = fmaxf(mx, fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])));
+        const float keep = mx == -INFINITY ? 0.f : __expf(mx - m);
+        den *= keep;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] *= keep;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float w = l[j] == -INFINITY ? 0.f : __expf(l[j] - m);
+            den += w;
+            acc[0] += w * v[j].x;
+            acc[1] += w * v[j].y;
+            acc[2] += w * v[j].z;
+            acc[3] += w * v[j].w;
+        }
+        mx = m;
     }
+    if (ways > 1) {  // the block's segment decides: uniform
+        __shared__ float4 s_acc[256];
+        __shared__ float2 s_md[GROUPS];
+        s_acc[threadIdx.x] = {acc[0], acc[1], acc[2], acc[3]};
+        if (c == 0) s_md[grp] = {mx, den};
+        __syncthreads();
+        if (way != 0) return;
+        float m = mx;
+        for (int w = 1; w < ways; ++w) m = fmaxf(m, s_md[grp + w].x);
+        const float keep = mx == -INFINITY ? 0.f : __expf(mx - m);
+        den *= keep;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] *= keep;
+        for (int w = 1; w < ways; ++w) {
+            const float2 md = s_md[grp + w];
+            const float4 v = s_acc[threadIdx.x + w * G];
+            const float f = md.x == -INFINITY ? 0.f : __expf(md.x - m);
+            den += f * md.y;
+            acc[0] += f * v.x;
+            acc[1] += f * v.y;
+            acc[2] += f * v.z;
+            acc[3] += f * v.w;
+        }
+        mx = m;
+    }
+    if (!valid) return;
     const float inv = 1.f / den;
     bf16x4 r;
 #pragma unroll
@@ -1313,6 +1386,7 @@ struct SegPlan {
     int32_t seg, row0, len, prefix, kv_start;
     int32_t tiles, pieces;
     bool paired;
+    int64_t longest;  // keys of the longest slot (of the last piece)
     int32_t slots() const { return paired ? (tiles + 1) / 2 : tiles; }
 };
 
@@ -1349,17 +1423,25 @@ bool supported_dims(int dqk, int dv) {
     return (dqk == 64 && dv == 64) || (dqk == 128 && dv == 128) || (dqk == 192 && dv == 128);
 }
 
-// Kernel variant for a chunk: query blocks of 32 rows per wave. 64-row waves
-// (NB = 2) unless the chunk is small and its key ranges short (at most two
-// 256-row workgroups per CU, at most 8192 keys per tile on average): there the
-// finer 128-row tiles (NB = 1, two workgroups per CU) even out the unequal
-// key ranges of the diagonal tiles. With dqk = 192 the 32-row variant runs out
-// of registers, so it keeps NB = 2. VPP_NB overrides, for tuning.
-int choose_nb(const vpp_chunk_attn_config_t& c, int64_t tiles256, double mean_keys256) {
+// Kernel variants a plan may choose from (bit nb - 1): query blocks of 32 rows per
+// wave. A chunk of at most two 256-row workgroups per CU and short key ranges (at
+// most 8192 keys per tile on average) takes the 128-row tiles (NB = 1, two
+// workgroups per CU), which even out the unequal key ranges of the diagonal tiles;
+// others take what the launch model below finds faster. With dqk = 192 the 32-row
+// waves spill a few registers, so they run only segments that would leave a 256-row
+// tile at least half empty: two workgroups a CU stream distinct keys at 5.9 TB/s
+// where one reaches 4.0. VPP_NB overrides, for tuning.
+bool small_chunk(const vpp_chunk_attn_config_t& c, int64_t tiles256, double mean_keys256) {
+    return c.head_dim_qk <= 128 && tiles256 * c.num_q_heads <= 2 * 256 && mean_keys256 <= 8192.0;
+}
+int forced_nb() {
     const char* e = getenv("VPP_NB");
-    if (e && (atoi(e) == 1 || atoi(e) == 2)) return atoi(e);
-    if (c.head_dim_qk <= 128 && tiles256 * c.num_q_heads <= 2 * 256 && mean_keys256 <= 8192.0) return 1;
-    return 2;
+    return e && (atoi(e) == 1 || atoi(e) == 2) ? atoi(e) : 0;
+}
+int allowed_nb(const vpp_chunk_attn_config_t& c, bool small, int64_t max_rows) {
+    if (forced_nb()) return forced_nb();
+    if (c.head_dim_qk > 128) return max_rows <= 128 ? 3 : 2;
+    return small ? 1 : 3;
 }
 
 // Query heads per tile: the largest divisor of Hq/Hkv up to 16. The heads that
@@ -1387,22 +1469,11 @@ vpp_status_t check_config(const vpp_chunk_attn_config_t& c) {
     return VPP_OK;
 }
 
-// Split count. A split cuts the prefix [0, p) of a segment into n tile-aligned
-// parts common to all of its tiles; the last part runs on to each tile's own end
-// (its keys within the chunk), so pieces of one index read the same keys in every
-// tile. Explicit: the requested count, at most one piece per key tile of the
-// longest prefix (a chunk without a prefix is not split). Automatic: the count
-// whose launch a model of the hardware's workgroup placement finishes first,
-// charging the fp32 partials that a split writes and the merge reads back
-// (see auto_split below); pieces hold at least MIN_PIECE prefix keys, and a
-// split must be predicted to gain at least 3 %.
-constexpr int64_t MIN_PIECE = 1024;
+// A fixed split request: at most one piece per key tile of the longest prefix (a
+// chunk without a prefix is not split), and of each segment's own.
 int fixed_splits(const vpp_chunk_attn_config_t& c, int64_t max_prefix) {
     return (int)std::min<int64_t>(c.num_splits, std::max<int64_t>(1, max_prefix / BN));
 }
-
-// Boundary b of the n-part split of a p-key prefix (tile-aligned, b = 0 .. n-1).
-int32_t piece_begin(int64_t p, int n, int b) { return (int32_t)(((p / BN) * b / n) * BN); }
 
 // Keys [begin, end) of piece b of n of a segment; end = INT32_MAX for the last.
 // A segment cut into fewer pieces than the plan's n has empty ones in front.
@@ -1425,111 +1496,277 @@ int64_t tile_keys(const SegPlan& s, int bm, int t, int32_t begin, int32_t end) {
     return std::max(0, std::min(own, end) - begin);
 }
 
-// A (segment, piece) in launch order: keys of its longest slot.
-struct PieceRef {
-    int32_t si, b, begin, end;  // si: index into the segment plans
-    int64_t keys;
-};
-
-// Every piece of every segment, longest first; empty pieces too if `all`.
-std::vector<PieceRef> launch_order(const std::vector<SegPlan>& segs, int n, int bm, bool all) {
-    std::vector<PieceRef> v;
-    v.reserve(segs.size() * (size_t)n);
-    for (size_t k = 0; k < segs.size(); ++k) {
-        const SegPlan& s = segs[k];
-        for (int b = 0; b < n; ++b) {
-            PieceRef r{(int32_t)k, b, 0, 0, 0};
-            piece_bounds(s, n, b, r.begin, r.end);
-            if (!all && r.begin == r.end) continue;
-            // a paired slot's two tiles together span the same keys in every slot but
-            // the first (whose partner may be short) and the middle one
-            const int last = s.slots() - 1;
-            for (int i : {0, std::min(1, last), last}) {
-                int64_t keys = tile_keys(s, bm, i, r.begin, r.end);
-                const int t = slot_tile(s, i, 1);
-                if (t >= 0) keys += tile_keys(s, bm, t, r.begin, r.end);
-                r.keys = std::max(r.keys, keys);
-            }
-            v.push_back(r);
-        }
+// Keys of the longest slot of a segment in [begin, end). A paired slot's two tiles
+// together span the same keys in every slot but the first (whose partner may be
+// short) and the middle one.
+int64_t longest_slot(const SegPlan& s, int tt, int32_t begin, int32_t end) {
+    const int last = s.slots() - 1;
+    int64_t best = 0;
+    for (int i : {0, std::min(1, last), last}) {
+        int64_t keys = tile_keys(s, tt, i, begin, end);
+        const int t = slot_tile(s, i, 1);
+        if (t >= 0) keys += tile_keys(s, tt, t, begin, end);
+        best = std::max(best, keys);
     }
-    std::stable_sort(v.begin(), v.end(), [](const PieceRef& x, const PieceRef& y) { return x.keys > y.keys; });
-    return v;
+    return best;
 }
 
-// Automatic split count: simulate the launch of each candidate count and keep
-// the fastest. The grid is the groups in launch order, each group's workgroups
-// dealt to the 8 XCDs alike (work_coords); each XCD places its workgroups in order
-// on whichever of its CU slots frees first (32 CUs, times the workgroups a CU
-// holds). A workgroup costs its key tiles plus a fixed amount per tile it runs (Q
-// load, pipeline fill, store). A split count n > 1 also costs the fp32 partials
-// its pieces write and the merge reads back. The unsplit plan is kept whenever its
-// simulated makespan is within 5 % of the ideal (total work spread evenly), which
-// covers every chunk with enough even slots.
-int auto_split(const vpp_chunk_attn_config_t& c, int nb, int pack, int tt, int64_t max_prefix, int32_t tokens,
-               std::vector<SegPlan>& segs) {
-    constexpr int NXCD = 8, CU_PER_XCD = 32;
-    constexpr double TILE_OVERHEAD = 2.0;  // fixed cost of a tile, in key tiles
-    const int heads = c.num_q_heads / pack, wg_per_cu = nb == 1 ? 2 : 1;
-    // one key tile of one workgroup: 2 rows BN (dqk + dv) flop at ~5 TFLOP/s per CU
-    const double tile_s = 2.0 * block_rows(nb) * BN * (c.head_dim_qk + c.head_dim_v) / 5.0e12;
-    auto entry_cost = [](int64_t keys) { return keys > 0 ? (double)((keys + BN - 1) / BN) + TILE_OVERHEAD : 0.0; };
-    // simulated seconds of the launch, and of its work spread evenly over the chip
-    auto simulate = [&](int n, double& ideal) {
-        for (SegPlan& s : segs) s.pieces = n;
-        const std::vector<PieceRef> order = launch_order(segs, n, tt, false);
-        const int lanes = CU_PER_XCD * wg_per_cu;
-        std::vector<std::vector<double>> costs;
-        double total = 0.0;
-        bool even = true;
-        for (const PieceRef& r : order) {
-            const SegPlan& s = segs[(size_t)r.si];
-            std::vector<double> v((size_t)s.slots());
-            for (int i = 0; i < s.slots(); ++i) {
-                v[(size_t)i] = entry_cost(tile_keys(s, tt, i, r.begin, r.end));
-                const int t = slot_tile(s, i, 1);
-                if (t >= 0) v[(size_t)i] += entry_cost(tile_keys(s, tt, t, r.begin, r.end));
-                total += v[(size_t)i] * heads;
-            }
-            even = even && (int64_t)s.slots() * heads % NXCD == 0;
-            costs.push_back(std::move(v));
-        }
-        ideal = total / (NXCD * lanes) * tile_s;
-        double makespan = 0.0;
-        // with whole eighths of every group per XCD, all XCDs run alike
-        for (int x = 0; x < (even ? 1 : NXCD); ++x) {
-            std::vector<double> free_at((size_t)lanes, 0.0);  // a min-heap of lane free times
-            int64_t wg0 = 0;
-            for (const std::vector<double>& v : costs) {
-                const int64_t nwg = (int64_t)v.size() * heads;
-                const int64_t r = ((x - wg0) % NXCD + NXCD) % NXCD;  // residue of this XCD's share
-                const int64_t first = r * (nwg / NXCD) + std::min(r, nwg % NXCD);
-                const int64_t share = nwg / NXCD + (r < nwg % NXCD ? 1 : 0);
-                for (int64_t j = 0; j < share; ++j) {
-                    std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
-                    free_at.back() += v[(size_t)((first + j) % (int64_t)v.size())];
-                    std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
+// ---- launch model -----------------------------------------------------------
+// What a plan may choose: the tile variant, one or two tiles per work slot, and the
+// pieces of every segment's prefix. The choice is the one whose launch this model
+// finishes first. Its constants are measured on one MI355X with normal operands.
+struct LaunchModel {
+    int heads, pack, dqk, dv;
+
+    // One 64-key step of a workgroup takes `few` us while few of them run. The chip as
+    // a whole finishes at most `rate` steps a us, held by power: past few * rate
+    // workgroups (three quarters of the CUs at dqk = 192) more of them in flight only
+    // slow each other down.
+    struct Speed { double few, rate; };
+    Speed speed(int nb) const {
+        static const Speed table[2][3] = {{{0.63, 427.0}, {0.83, 277.0}, {1.20, 213.0}},
+                                          {{1.03, 233.0}, {1.30, 149.0}, {1.65, 125.0}}};
+        return table[nb - 1][dqk == 64 ? 0 : dqk == 128 ? 1 : 2];
+    }
+    // What a tile costs beside its steps, in steps: Q load, pipeline fill, first and
+    // last step, store. Two 128-row workgroups a CU hide much of each other's.
+    double tile(int nb) const { return nb == 1 ? 2.5 : 5.0; }
+    // The rate at which workgroups stream distinct keys, one or two in flight per CU:
+    // it holds back the steps of segments with few tiles.
+    double stream(int nb) const { return nb == 1 ? 5.5e6 : 3.8e6; }  // bytes per us
+    static constexpr int NUM_CU = 256, NXCD = 8;
+
+    // Time of the merge of part_rows partial rows: a launch, and the partials written
+    // and read back.
+    double merge(int64_t part_rows) const {
+        return part_rows == 0 ? 0.0 : 5.0 + 2.0 * (double)part_rows * heads * (4.0 * dv + 4.0) / 5.0e6;
+    }
+
+    // Time of a launch of `segs` (longest slots first): one XCD's share of each group
+    // (work_coords), placed in order on whichever of its workgroup places frees first.
+    // All places progress alike, so the schedule is found in steps and then put on the
+    // clock. While any CU holds two 128-row workgroups those two set the pace.
+    double launch(const std::vector<SegPlan>& segs, int nb, int tt, std::vector<double>& lanes) const {
+        const int64_t groups = heads / pack;
+        const int places = NUM_CU / NXCD * (3 - nb);
+        const double c_tile = tile(nb);
+        double bytes = 0.0;
+        lanes.assign((size_t)places, 0.0);
+        int64_t seen = 0;
+        for (const SegPlan& s : segs) {
+            bytes += (double)groups * ((double)s.prefix + s.len) * (dqk + dv) * 2.0;
+            const int64_t n = s.slots() * groups * s.pieces;
+            int64_t share = (seen + n + NXCD - 1) / NXCD - (seen + NXCD - 1) / NXCD;
+            seen += n;
+            int32_t kb = 0, ke = INT32_MAX;
+            auto cost = [&](int i) {
+                double t = 0.0;
+                for (int which = 0; which < 2; ++which) {
+                    const int tl = slot_tile(s, i, which);
+                    if (tl >= 0) t += (double)((tile_keys(s, tt, tl, kb, ke) + BN - 1) / BN) + c_tile;
                 }
-                wg0 += nwg;
+                return t;
+            };
+            // every `stride`-th slot of its heads, longest first where slots are single tiles
+            const int64_t h = groups * s.pieces;
+            const int stride = s.paired ? 1 : (int)(NXCD / std::min<int64_t>(NXCD, h & -h));
+            int skip = 0;
+            // many rounds of one segment fill the places evenly: only the last few are
+            // placed, taken evenly from its slots
+            if (share > 8 * places) {
+                double sum = 0.0;
+                const int period = std::min(s.slots(), 16);
+                for (int i = 0; i < period; ++i) sum += cost((int)((int64_t)i * s.slots() / period));
+                sum /= (double)period * s.pieces;  // the pieces of a slot together cost about the whole
+                const int64_t whole = share / places - 4;
+                for (double& t : lanes) t += sum * (double)whole;
+                skip = (int)(share / (share - whole * places)) - 1;
+                share -= whole * places;
             }
+            int piece = s.pieces - 1, slot = 0;
+            auto bounds = [&]() {
+                if (s.pieces == 1) return;
+                kb = piece_begin(s.prefix, s.pieces, piece);
+                ke = piece + 1 == s.pieces ? INT32_MAX : piece_begin(s.prefix, s.pieces, piece + 1);
+            };
+            bounds();
+            for (int64_t j = 0; j < share; ++j) {
+                std::pop_heap(lanes.begin(), lanes.end(), std::greater<double>());
+                lanes.back() += cost(s.paired ? slot : s.slots() - 1 - slot);
+                std::push_heap(lanes.begin(), lanes.end(), std::greater<double>());
+                for (slot += stride * (1 + skip); slot >= s.slots(); slot -= s.slots()) {
+                    piece = piece == 0 ? s.pieces - 1 : piece - 1;
+                    bounds();
+                }
+            }
+        }
+        double steps = 0.0;
+        for (double l : lanes) steps += l * NXCD;
+        std::sort(lanes.begin(), lanes.end());
+        Speed v = speed(nb);
+        v.rate = std::min(v.rate, stream(nb) * steps / bytes);
+        double t = 0.0, at = 0.0;
+        for (int i = 0; i < places; ++i) {
+            const int active = places - i > NUM_CU / NXCD ? places : places - i;
+            t += (lanes[(size_t)i] - at) * std::max(v.few, (double)active * NXCD / v.rate);
+            at = lanes[(size_t)i];
+        }
+        return t;
+    }
+};
+
+// A candidate plan and its modelled time.
+struct Candidate {
+    std::vector<SegPlan> segs;
+    int nb = 2, tt = 256;
+    double t = 0.0;
+    int64_t part_rows() const {
+        int64_t n = 0;
+        for (const SegPlan& s : segs) n += s.pieces > 1 ? (int64_t)s.pieces * s.len : 0;
+        return n;
+    }
+};
+
+size_t partial_bytes(const vpp_chunk_attn_config_t& c, int64_t part_rows) {
+    return align256((size_t)part_rows * c.num_q_heads * c.head_dim_v * sizeof(float)) +
+           align256((size_t)part_rows * c.num_q_heads * sizeof(float));
+}
+
+// Plan of the segments `segs` (rows set, the rest chosen here); an automatic split
+// takes at most max_part bytes of partials.
+Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPlan>& segs, int nb_mask, int pack,
+                      size_t max_part) {
+    constexpr int MAX_PIECES = 64;
+    constexpr int64_t MIN_PIECE = 4 * BN;  // keys of prefix a piece holds at least
+    const LaunchModel model{c.num_q_heads, pack, c.head_dim_qk, c.head_dim_v};
+    const int64_t groups = c.num_q_heads / pack;
+    int64_t max_prefix = 0;
+    for (const SegPlan& s : segs) max_prefix = std::max<int64_t>(max_prefix, s.prefix);
+    const int fixed = c.num_splits >= 1 ? fixed_splits(c, max_prefix) : 0;
+    Candidate best, x;
+    std::vector<double> lanes;
+    // Candidates compare by their modelled time and what it leaves out: a pair's tiles
+    // share their key reads with the other slots of the segment, 4 to 8 % of a long
+    // launch, and a split must be worth its partials' memory.
+    double best_score = 0.0;
+    auto consider = [&](bool paired, bool split) {
+        if (!fixed && !best.segs.empty() && partial_bytes(c, x.part_rows()) > max_part) return;
+        for (SegPlan& s : x.segs)
+            s.longest = longest_slot(s, x.tt, s.pieces > 1 ? piece_begin(s.prefix, s.pieces, s.pieces - 1) : 0, INT32_MAX);
+        std::stable_sort(x.segs.begin(), x.segs.end(),
+                         [](const SegPlan& a, const SegPlan& b) { return a.longest > b.longest; });
+        x.t = model.launch(x.segs, x.nb, x.tt, lanes) + model.merge(x.part_rows());
+        const double score = x.t * (1.0 + (split ? 0.02 : 0.0) + (!paired && x.t > 400.0 ? 0.04 : 0.0));
+        if (best.segs.empty() || score < best_score) {
+            best = x;
+            best_score = score;
+        }
+    };
+    for (int nb : {2, 1}) {
+        if (!(nb_mask & nb)) continue;
+        x.nb = nb;
+        x.tt = block_rows(nb) / pack;
+        // the launch's work if spread evenly: steps of one workgroup place, and its time
+        double steps = 0.0, bytes = 0.0;
+        for (const SegPlan& s : segs) {
+            steps += (double)groups * ((s.len + x.tt - 1) / x.tt) * (((double)s.prefix + 0.5 * s.len) / BN + 1.0);
+            bytes += (double)groups * ((double)s.prefix + s.len) * (c.head_dim_qk + c.head_dim_v) * 2.0;
+        }
+        const double even = steps / (LaunchModel::NUM_CU * (3 - nb));
+        const double bound = std::max(steps / model.speed(nb).rate, bytes / model.stream(nb));
+        for (int paired = 1; paired >= 0; --paired) {
+            x.segs = segs;
+            for (SegPlan& s : x.segs) {
+                s.tiles = (int32_t)(((int64_t)s.len + x.tt - 1) / x.tt);
+                s.paired = paired != 0;
+                s.pieces = fixed > 1 ? (int)std::min<int64_t>(fixed, std::max(1, s.prefix / BN)) : 1;
+            }
+            consider(paired != 0, false);
+            if (fixed || best.t < 1.08 * bound) continue;
+            double last_t = 1e30;
+            for (double f : {2.0, 1.0, 0.7, 0.5, 0.35, 0.25, 0.17, 0.12}) {
+                const double target = std::max(even * f, 4.0);  // steps of a workgroup
+                bool split = false;
+                for (SegPlan& s : x.segs) {
+                    s.pieces = 1;
+                    const double longest = (double)longest_slot(s, x.tt, 0, INT32_MAX) / BN;
+                    const int64_t cap = std::min<int64_t>(MAX_PIECES, s.prefix / MIN_PIECE);
+                    s.pieces = (int)std::max<int64_t>(1, std::min<int64_t>(cap, (int64_t)ceil(longest / target)));
+                    split = split || s.pieces > 1;
+                }
+                if (!split) continue;
+                consider(paired != 0, true);
+                if (target <= 4.0 || (x.t > last_t && x.t > 1.1 * best.t) || best.t < 1.08 * bound) break;
+                last_t = x.t;
+            }
+        }
+    }
+    return best;
+}
+
+// The split count of one-head tiles run in pairs, from a launch placed head by head:
+// the rule by which a plan's workspace fits vpp_chunk_attn_run_noalloc's scratch or not.
+// A chunk whose workspace it keeps within the scratch stays within it (split_limit).
+int one_head_splits(const vpp_chunk_attn_config_t& c, std::vector<SegPlan> segs, int nb, int64_t max_prefix,
+                    int32_t tokens) {
+    constexpr int NXCD = LaunchModel::NXCD;
+    constexpr double TILE = 2.0;  // fixed cost of a tile, in steps
+    const int bm = block_rows(nb), heads = c.num_q_heads;
+    const double step_s = 2.0 * bm * BN * (c.head_dim_qk + c.head_dim_v) / 5.0e12;
+    std::vector<double> cost, free_at;
+    auto simulate = [&](int n, double& ideal) {
+        struct Group { int si, b; int64_t keys; };
+        std::vector<Group> order;
+        for (size_t k = 0; k < segs.size(); ++k) {
+            segs[k].tiles = (int32_t)(((int64_t)segs[k].len + bm - 1) / bm);
+            segs[k].paired = true;
+            for (int b = 0; b < n; ++b) {
+                const int32_t kb = n == 1 ? 0 : piece_begin(segs[k].prefix, n, b);
+                const int32_t ke = b + 1 == n ? INT32_MAX : piece_begin(segs[k].prefix, n, b + 1);
+                order.push_back({(int)k, b, longest_slot(segs[k], bm, kb, ke)});
+            }
+        }
+        std::stable_sort(order.begin(), order.end(), [](const Group& x, const Group& y) { return x.keys > y.keys; });
+        cost.clear();
+        double total = 0.0;
+        for (const Group& g : order) {
+            const SegPlan& s = segs[(size_t)g.si];
+            const int32_t kb = n == 1 ? 0 : piece_begin(s.prefix, n, g.b);
+            const int32_t ke = g.b + 1 == n ? INT32_MAX : piece_begin(s.prefix, n, g.b + 1);
+            for (int i = 0; i < s.slots(); ++i) {
+                double t = 0.0;
+                for (int which = 0; which < 2; ++which)
+                    if (slot_tile(s, i, which) >= 0)
+                        t += (double)((tile_keys(s, bm, slot_tile(s, i, which), kb, ke) + BN - 1) / BN) + TILE;
+                cost.push_back(t);
+                total += t;
+            }
+        }
+        const int64_t nslots = (int64_t)cost.size(), all = nslots * heads, per = all / NXCD;
+        const size_t lanes = (size_t)(LaunchModel::NUM_CU / NXCD * (3 - nb));
+        ideal = total * heads / (double)(NXCD * lanes) * step_s;
+        double makespan = 0.0;
+        for (int x = 0; x < (heads % NXCD == 0 ? 1 : NXCD); ++x) {
+            free_at.assign(lanes, 0.0);
+            auto place = [&](int64_t l) {
+                std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
+                free_at.back() += cost[(size_t)(l % nslots)];
+                std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
+            };
+            for (int64_t j = 0; j < per; ++j) place(x * per + j);
+            for (int64_t l = per * NXCD + x; l < all; l += NXCD) place(l);
             makespan = std::max(makespan, *std::max_element(free_at.begin(), free_at.end()));
         }
-        return makespan * tile_s;
+        return makespan * step_s;
     };
-    double ideal1 = 0.0;
-    const double t1 = simulate(1, ideal1);
-    if (t1 <= 1.05 * ideal1) return 1;
-    const int64_t cap = std::min<int64_t>(MAX_SPLITS, max_prefix / MIN_PIECE);
-    // partial bytes per piece: fp32 out and lse of every (row, head), written once and
-    // read once, at the ~3 TB/s the split chunks of the mixed workload were measured to
-    // pay; a split must also be predicted to gain at least 3 %
-    const double partial_s = 2.0 * tokens * c.num_q_heads * (4.0 * c.head_dim_v + 4.0) / 3.0e12;
+    double ideal = 0.0;
+    const double t1 = simulate(1, ideal);
+    if (t1 <= 1.05 * ideal) return 1;
+    const double partial_s = 2.0 * tokens * heads * (4.0 * c.head_dim_v + 4.0) / 3.0e12;
     int best = 1;
     double best_t = 0.97 * t1;
-    static const int candidates[] = {2, 3, 4, 6, 8, 12, 16};
-    for (int n : candidates) {
-        if (n > cap) break;
-        double ideal = 0.0;
+    for (int n : {2, 3, 4, 6, 8, 12, 16}) {
+        if (n > std::min<int64_t>(MAX_SPLITS, max_prefix / 1024)) break;
         const double t = simulate(n, ideal) + n * partial_s;
         if (t < best_t) {
             best_t = t;
@@ -1577,76 +1814,69 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
             ++tiles256;
             keys256 += (double)prefix_len[s] + (r0 - cu_q[s]) + std::min(block_rows(2), cu_q[s + 1] - r0);
         }
-    const int nb = choose_nb(c, tiles256, tiles256 ? keys256 / tiles256 : 0.0);
     const int pack = heads_per_tile(c);
-    const int tt = block_rows(nb) / pack;  // tokens per tile
-    // Work slots. A workgroup runs one slot: up to two query tiles of one segment,
+    // Work slots. A workgroup runs one slot: one query tile, or two of one segment,
     // tile i with its key range ascending, then tile T-1-i (the partner from the
     // other end of the segment) descending. A pair's two ranges together span the
     // same number of keys in every slot of the segment, so the workgroups of a
     // segment finish together; and at any moment they all read one of two key
     // positions (the ascending front, and the descending one, which mirrors it), so
     // the tiles running side by side on one XCD share each K/V tile through its L2.
-    // Slots are grouped by (segment, split piece); groups run longest first.
-    std::vector<SegPlan> segs;
+    Candidate plan;
     std::vector<LaunchGroup> groups;
     std::vector<CombineSeg> merges;
     double pairs = 0.0;
     int64_t ntiles = 0, nslots = 0, wgs = 0, part_rows = 0, blocks = 0;
     int nsplit = 1;
     try {
-        int64_t max_prefix = 0;
+        std::vector<SegPlan> segs;
+        int64_t max_rows = 0, max_prefix = 0;
         for (int s = 0; s < num_segments; ++s) {
             const int32_t len = cu_q[s + 1] - cu_q[s];
             if (len == 0) continue;
-            SegPlan sp{s, cu_q[s], len, (int32_t)prefix_len[s], (int32_t)kv_start[s], 
-                       (int32_t)(((int64_t)len + tt - 1) / tt), 1, true};
+            segs.push_back({s, cu_q[s], len, (int32_t)prefix_len[s], (int32_t)kv_start[s], 0, 1, true, 0});
             // visible pairs: sum over rows of (position + 1)
             pairs += (double)len * (double)prefix_len[s] + 0.5 * (double)len * (len + 1.0);
-            ntiles += sp.tiles;
+            max_rows = std::max<int64_t>(max_rows, (int64_t)len * pack);
             max_prefix = std::max(max_prefix, prefix_len[s]);
-            segs.push_back(sp);
         }
-        // a pair of tiles shares reads only where the chip is full: with fewer tiles
-        // than workgroups fit, each runs alone and finishes in half the time
-        for (SegPlan& s : segs) {
-            s.paired = ntiles * (c.num_q_heads / pack) > 256 * (3 - nb);
-            nslots += s.slots();
-        }
-        if (!segs.empty())
-            nsplit = c.num_splits >= 1 ? fixed_splits(c, max_prefix)
-                                       : auto_split(c, nb, pack, tt, max_prefix, cu_q[num_segments], segs);
-        for (SegPlan& s : segs) s.pieces = nsplit;
-
-        // partial rows of the split segments, piece by piece; a segment with one piece
-        // that has keys writes its results directly
-        std::vector<int32_t> next_part(segs.size(), -1);
-        for (size_t k = 0; k < segs.size(); ++k) {
-            int pieces = 0;
-            for (int b = 0; b < nsplit; ++b) {
-                int32_t kb, ke;
-                piece_bounds(segs[k], nsplit, b, kb, ke);
-                pieces += kb != ke;
+        if (!segs.empty()) {
+            const bool small = small_chunk(c, tiles256, keys256 / tiles256);
+            const int nb_mask = allowed_nb(c, small, max_rows);
+            plan = choose_plan(c, segs, nb_mask, pack, SIZE_MAX);
+            // a chunk that one-head tiles in pairs would keep within the scratch of
+            // run_noalloc stays within it
+            const size_t room = VPP_NOALLOC_SCRATCH_BYTES - (4u << 20);
+            if (c.num_splits < 1 && partial_bytes(c, plan.part_rows()) > room) {
+                const int one_head_nb = forced_nb() ? forced_nb() : small ? 1 : 2;
+                const int n = one_head_splits(c, segs, one_head_nb, max_prefix, cu_q[num_segments]);
+                if (n == 1 || partial_bytes(c, (int64_t)n * cu_q[num_segments]) <= VPP_NOALLOC_SCRATCH_BYTES)
+                    plan = choose_plan(c, segs, nb_mask, pack, room);
             }
-            if (pieces < 2) continue;
-            next_part[k] = (int32_t)part_rows;
-            merges.push_back({(int32_t)blocks, segs[k].row0, segs[k].len, pieces, (int32_t)part_rows});
-            part_rows += (int64_t)pieces * segs[k].len;
-            blocks += ((int64_t)segs[k].len * c.num_q_heads * (c.head_dim_v / 4) + 255) / 256;
         }
-        for (const PieceRef& r : launch_order(segs, nsplit, tt, false)) {
-            const SegPlan& s = segs[(size_t)r.si];
-            LaunchGroup g{(int32_t)wgs, s.row0, s.len, s.prefix, s.kv_start, r.begin, r.end, s.seg, -1, s.slots(), s.tiles};
-            if (next_part[(size_t)r.si] >= 0) {
-                g.part0 = next_part[(size_t)r.si];
-                next_part[(size_t)r.si] += s.len;
+        if (c.num_splits >= 1 && !segs.empty()) nsplit = fixed_splits(c, max_prefix);
+        else
+            for (const SegPlan& s : plan.segs) nsplit = std::max(nsplit, s.pieces);
+        // partial rows of the split segments, piece by piece; a segment of one piece
+        // writes its results directly
+        for (const SegPlan& s : plan.segs) {
+            LaunchGroup g{(int32_t)wgs, s.row0, s.len, s.prefix, s.kv_start, s.seg, s.pieces, -1, s.slots(), s.tiles};
+            if (s.pieces > 1) {
+                g.part0 = (int32_t)part_rows;
+                merges.push_back({(int32_t)blocks, s.row0, s.len, s.pieces, (int32_t)part_rows});
+                part_rows += (int64_t)s.pieces * s.len;
+                const int64_t per_block = 1024 / c.head_dim_v / merge_ways(s.pieces);  // (row, head) pairs
+                blocks += ((int64_t)s.len * c.num_q_heads + per_block - 1) / per_block;
             }
             groups.push_back(g);
-            wgs += (int64_t)g.slots * (c.num_q_heads / pack);
+            wgs += (int64_t)g.slots * s.pieces * (c.num_q_heads / pack);
+            ntiles += s.tiles;
+            nslots += s.slots();
         }
     } catch (const std::bad_alloc&) {
         return VPP_ERR_NOMEM;
     }
+    const int nb = plan.nb, tt = block_rows(nb) / pack;
 
     if (!p) {
         p = new (std::nothrow) vpp_chunk_attn_plan_s();
@@ -1658,7 +1888,7 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
     p->pack = pack;
     p->tile_tokens = tt;
     p->scale = c.softmax_scale > 0.f ? c.softmax_scale : (float)(1.0 / sqrt((double)c.head_dim_qk));
-    p->segs.swap(segs);
+    p->segs.swap(plan.segs);
     p->groups.swap(groups);
     p->merges.swap(merges);
     p->merge_blocks = (int32_t)blocks;
@@ -1702,9 +1932,25 @@ extern "C" vpp_status_t vpp_chunk_attn_plan_items(vpp_chunk_attn_plan_t p, vpp_c
     if (capacity == 0) return VPP_OK;
     const int bm = p->tile_tokens;
     int32_t n = 0;
+    // (segment, piece) pairs, longest slot first; the empty pieces of segments cut
+    // into fewer than num_splits are listed too
+    struct Piece {
+        const SegPlan* s;
+        int32_t b, begin, end;
+        int64_t keys;
+    };
     try {
-        for (const PieceRef& r : launch_order(p->segs, p->num_splits, bm, true)) {
-            const SegPlan& s = p->segs[(size_t)r.si];
+        std::vector<Piece> order;
+        for (const SegPlan& s : p->segs)
+            for (int b = 0; b < p->num_splits; ++b) {
+                Piece r{&s, b, 0, 0, 0};
+                piece_bounds(s, p->num_splits, b, r.begin, r.end);
+                r.keys = longest_slot(s, bm, r.begin, r.end);
+                order.push_back(r);
+            }
+        std::stable_sort(order.begin(), order.end(), [](const Piece& x, const Piece& y) { return x.keys > y.keys; });
+        for (const Piece& r : order) {
+            const SegPlan& s = *r.s;
             for (int i = 0; i < s.slots(); ++i)
                 for (int which = 0; which < 2; ++which) {
                     if (n == capacity) return VPP_OK;

@@ -1,6 +1,6 @@
 """Chunks of many segments: the launch table around its limits, against the fp64 oracle.
 
-A run's launch table has one entry per segment and split piece that has keys. Up to 64
+A run's launch table has one entry per segment that has rows. Up to 64
 entries travel in the kernel arguments, more are copied to the workspace; a workgroup finds
 its entry by comparing 64 at a time, so 64/65 and 4096/4097 are where the search takes
 another step. Segments without a prefix have one piece whatever the split count and write
@@ -28,9 +28,9 @@ def _rand(shape, seed):
 @pytest.mark.parametrize("nseg,rows,prefix,heads,splits", [
     (64, 3, 0, (4, 2), 1),
     (65, 3, 0, (4, 2), 1),
-    (33, 5, 130, (3, 1), 2),     # 44 pieces of 33 segments
-    (60, 2, 200, (4, 4), 3),     # 100 pieces, 20 merged segments
-    (200, 1, 140, (2, 1), 2),    # 267 pieces, 67 merged segments
+    (33, 5, 130, (3, 1), 2),     # 11 merged segments
+    (60, 2, 200, (4, 4), 3),     # 20 merged segments
+    (200, 1, 140, (2, 1), 2),    # 67 merged segments
     (4096, 1, 0, (1, 1), 1),
     (4097, 1, 0, (2, 1), 1),
     (3, 300, 700, (4, 2), -1),
@@ -60,3 +60,33 @@ def test_many_segments(nseg, rows, prefix, heads, splits):
     attn.run_noalloc(q, k, v, out2, lse2)
     torch.cuda.synchronize()
     assert torch.equal(out, out2) and torch.equal(lse, lse2)
+
+
+# pieces per segment: 2, 5, 9, 16 (the merge walks them one, two, four and eight ways), and
+# automatic plans of few rows behind long prefixes, whose segments are cut each on its own
+@pytest.mark.parametrize("heads,dims,segs,splits", [
+    ((4, 2), (128, 128), [(2000, 37)], 2),
+    ((4, 2), (128, 128), [(2000, 37), (300, 5)], 5),
+    ((3, 3), (64, 64), [(2000, 37), (70, 9)], 9),
+    ((2, 2), (192, 128), [(2000, 37), (0, 200)], 16),
+    ((4, 4), (64, 64), [(20000, 3)], -1),
+    ((4, 1), (128, 128), [(9000, 217), (40, 300)], -1),
+    ((8, 2), (128, 128), [(6000, 40), (3000, 1), (0, 700), (100, 1)], -1),
+    ((16, 16), (192, 128), [(5000, 60), (700, 1)], -1),
+])
+def test_pieces_and_merge(heads, dims, segs, splits):
+    from paper_2608_26523_amd.attention import ChunkAttention
+    (hq, hkv), (dqk, dv) = heads, dims
+    kvs = [int(x) for x in np.cumsum([0] + [p + n for p, n in segs[:-1]])]
+    T = sum(p + n for p, n in segs)
+    cu = np.cumsum([0] + [n for _, n in segs])
+    tok = int(cu[-1])
+    print("case:", heads, dims, segs, splits, flush=True)
+    q, k, v = _rand((tok, hq, dqk), 1), _rand((T, hkv, dqk), 2), _rand((T, hkv, dv), 3)
+    attn = ChunkAttention(hq, hkv, dqk, dv, max_chunk_tokens=tok, max_kv_len=T, num_splits=splits)
+    out, lse = PA.run_chunk(attn, q, k, v, cu, kvs, [p for p, _ in segs])
+    assert attn.info().num_splits == splits if splits > 0 else attn.info().num_splits > 1
+    ro, rl = oracle.attention_full(q.cpu(), k.cpu(), v.cpu(), cu, kvs, [p for p, _ in segs])
+    r, h = np.repeat(np.arange(tok), hq), np.tile(np.arange(hq), tok)
+    rep = PA.compare(out, lse, r, h, ro.reshape(tok * hq, -1), rl.T.reshape(-1))
+    assert rep.ok(), str(rep)
