@@ -67,9 +67,6 @@ constexpr float LAZY_TAU = 8.0f;
 // The next tiles' global->LDS copies are spread over the first 1/LOAD_SPREAD
 // of a tile's MFMA slots.
 constexpr int LOAD_SPREAD = 2;
-// LDS fragment prefetch distances (in fragments) of the K and V^T operands
-constexpr int K_AHEAD = 3;
-constexpr int V_AHEAD = 2;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -307,6 +304,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // Tables that travel in the kernel arguments or in device memory, read as
 // constant memory: uniform indices become scalar loads.
+typedef __attribute__((address_space(4))) const AttnArgs const_args_t;
 typedef __attribute__((address_space(4))) const LaunchGroup const_group_t;
 typedef __attribute__((address_space(4))) const CombineSeg const_seg_t;
 template <typename T>
@@ -347,10 +345,10 @@ __device__ __forceinline__ void work_coords(int i, int slots, int heads, bool pa
         const int x = i & 7;
         i = x * (n >> 3) + min(x, n & 7) + (i >> 3);
     } else if (remap) {
-        const int g = min(8, heads & -heads);  // XCDs x and x + g share heads
-        i = (i & (g - 1)) * (heads / g) * slots + i / g;
+        const int g = min(3, __builtin_ctz(heads));  // XCDs x and x + 2^g share heads
+        i = (i & ((1 << g) - 1)) * (heads >> g) * slots + (i >> g);
     }
-    head = i / slots;
+    head = slots == 1 ? i : i / slots;
     slot = i - head * slots;
     if (!paired) slot = slots - 1 - slot;
 }
@@ -521,21 +519,39 @@ __device__ __forceinline__ void mfma_drain() {
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
 }
 
-// Load the KS B-operand fragments of one query row (16 bytes each, 32 bytes
-// apart) straight into AGPRs, where only MFMAs read them. Loading through
-// VGPRs would leave a VGPR copy of Q alive across the whole loop.
-template <int KS>
-__device__ __forceinline__ void load_q_agpr(bf16x8 (&qf)[KS], const void* p) {
+// Load the KS B-operand fragments of a lane's NB query rows (16 bytes each, 32
+// bytes apart) straight into AGPRs, where only MFMAs read them. Loading through
+// VGPRs would leave a VGPR copy of Q alive across the whole loop. The wait stands in
+// the same statement: the compiler takes the registers as written when it ends. It
+// also covers the tile's first K and V copies, issued just before.
+template <int KS, int NB>
+__device__ __forceinline__ void load_q_agpr(bf16x8 (&qf)[NB][KS], const u16* const (&p)[NB]) {
     static_assert(KS == 4 || KS == 8 || KS == 12, "head dims 64, 128, 192");
-    if constexpr (KS == 4) {
+    static_assert(NB == 1 || NB == 2, "query rows of a lane");
+    if constexpr (KS == 4 && NB == 1) {
         asm volatile(
             "global_load_dwordx4 %0, %4, off\n\t"
             "global_load_dwordx4 %1, %4, off offset:32\n\t"
             "global_load_dwordx4 %2, %4, off offset:64\n\t"
-            "global_load_dwordx4 %3, %4, off offset:96"
-            : "=a"(qf[0]), "=a"(qf[1]), "=a"(qf[2]), "=a"(qf[3])
-            : "v"(p) : "memory");
-    } else if constexpr (KS == 8) {
+            "global_load_dwordx4 %3, %4, off offset:96\n\t"
+            "s_waitcnt vmcnt(0)"
+            : "=a"(qf[0][0]), "=a"(qf[0][1]), "=a"(qf[0][2]), "=a"(qf[0][3])
+            : "v"(p[0]) : "memory");
+    } else if constexpr (KS == 4 && NB == 2) {
+        asm volatile(
+            "global_load_dwordx4 %0, %8, off\n\t"
+            "global_load_dwordx4 %1, %8, off offset:32\n\t"
+            "global_load_dwordx4 %2, %8, off offset:64\n\t"
+            "global_load_dwordx4 %3, %8, off offset:96\n\t"
+            "global_load_dwordx4 %4, %9, off\n\t"
+            "global_load_dwordx4 %5, %9, off offset:32\n\t"
+            "global_load_dwordx4 %6, %9, off offset:64\n\t"
+            "global_load_dwordx4 %7, %9, off offset:96\n\t"
+            "s_waitcnt vmcnt(0)"
+            : "=a"(qf[0][0]), "=a"(qf[0][1]), "=a"(qf[0][2]), "=a"(qf[0][3]), "=a"(qf[1][0]),
+              "=a"(qf[1][1]), "=a"(qf[1][2]), "=a"(qf[1][3])
+            : "v"(p[0]), "v"(p[1]) : "memory");
+    } else if constexpr (KS == 8 && NB == 1) {
         asm volatile(
             "global_load_dwordx4 %0, %8, off\n\t"
             "global_load_dwordx4 %1, %8, off offset:32\n\t"
@@ -544,11 +560,35 @@ __device__ __forceinline__ void load_q_agpr(bf16x8 (&qf)[KS], const void* p) {
             "global_load_dwordx4 %4, %8, off offset:128\n\t"
             "global_load_dwordx4 %5, %8, off offset:160\n\t"
             "global_load_dwordx4 %6, %8, off offset:192\n\t"
-            "global_load_dwordx4 %7, %8, off offset:224"
-            : "=a"(qf[0]), "=a"(qf[1]), "=a"(qf[2]), "=a"(qf[3]), "=a"(qf[4]), "=a"(qf[5]),
-              "=a"(qf[6]), "=a"(qf[7])
-            : "v"(p) : "memory");
-    } else {
+            "global_load_dwordx4 %7, %8, off offset:224\n\t"
+            "s_waitcnt vmcnt(0)"
+            : "=a"(qf[0][0]), "=a"(qf[0][1]), "=a"(qf[0][2]), "=a"(qf[0][3]), "=a"(qf[0][4]),
+              "=a"(qf[0][5]), "=a"(qf[0][6]), "=a"(qf[0][7])
+            : "v"(p[0]) : "memory");
+    } else if constexpr (KS == 8 && NB == 2) {
+        asm volatile(
+            "global_load_dwordx4 %0, %16, off\n\t"
+            "global_load_dwordx4 %1, %16, off offset:32\n\t"
+            "global_load_dwordx4 %2, %16, off offset:64\n\t"
+            "global_load_dwordx4 %3, %16, off offset:96\n\t"
+            "global_load_dwordx4 %4, %16, off offset:128\n\t"
+            "global_load_dwordx4 %5, %16, off offset:160\n\t"
+            "global_load_dwordx4 %6, %16, off offset:192\n\t"
+            "global_load_dwordx4 %7, %16, off offset:224\n\t"
+            "global_load_dwordx4 %8, %17, off\n\t"
+            "global_load_dwordx4 %9, %17, off offset:32\n\t"
+            "global_load_dwordx4 %10, %17, off offset:64\n\t"
+            "global_load_dwordx4 %11, %17, off offset:96\n\t"
+            "global_load_dwordx4 %12, %17, off offset:128\n\t"
+            "global_load_dwordx4 %13, %17, off offset:160\n\t"
+            "global_load_dwordx4 %14, %17, off offset:192\n\t"
+            "global_load_dwordx4 %15, %17, off offset:224\n\t"
+            "s_waitcnt vmcnt(0)"
+            : "=a"(qf[0][0]), "=a"(qf[0][1]), "=a"(qf[0][2]), "=a"(qf[0][3]), "=a"(qf[0][4]),
+              "=a"(qf[0][5]), "=a"(qf[0][6]), "=a"(qf[0][7]), "=a"(qf[1][0]), "=a"(qf[1][1]),
+              "=a"(qf[1][2]), "=a"(qf[1][3]), "=a"(qf[1][4]), "=a"(qf[1][5]), "=a"(qf[1][6]), "=a"(qf[1][7])
+            : "v"(p[0]), "v"(p[1]) : "memory");
+    } else if constexpr (KS == 12 && NB == 1) {
         asm volatile(
             "global_load_dwordx4 %0, %12, off\n\t"
             "global_load_dwordx4 %1, %12, off offset:32\n\t"
@@ -561,10 +601,45 @@ __device__ __forceinline__ void load_q_agpr(bf16x8 (&qf)[KS], const void* p) {
             "global_load_dwordx4 %8, %12, off offset:256\n\t"
             "global_load_dwordx4 %9, %12, off offset:288\n\t"
             "global_load_dwordx4 %10, %12, off offset:320\n\t"
-            "global_load_dwordx4 %11, %12, off offset:352"
-            : "=a"(qf[0]), "=a"(qf[1]), "=a"(qf[2]), "=a"(qf[3]), "=a"(qf[4]), "=a"(qf[5]),
-              "=a"(qf[6]), "=a"(qf[7]), "=a"(qf[8]), "=a"(qf[9]), "=a"(qf[10]), "=a"(qf[11])
-            : "v"(p) : "memory");
+            "global_load_dwordx4 %11, %12, off offset:352\n\t"
+            "s_waitcnt vmcnt(0)"
+            : "=a"(qf[0][0]), "=a"(qf[0][1]), "=a"(qf[0][2]), "=a"(qf[0][3]), "=a"(qf[0][4]),
+              "=a"(qf[0][5]), "=a"(qf[0][6]), "=a"(qf[0][7]), "=a"(qf[0][8]), "=a"(qf[0][9]),
+              "=a"(qf[0][10]), "=a"(qf[0][11])
+            : "v"(p[0]) : "memory");
+    } else if constexpr (KS == 12 && NB == 2) {
+        asm volatile(
+            "global_load_dwordx4 %0, %24, off\n\t"
+            "global_load_dwordx4 %1, %24, off offset:32\n\t"
+            "global_load_dwordx4 %2, %24, off offset:64\n\t"
+            "global_load_dwordx4 %3, %24, off offset:96\n\t"
+            "global_load_dwordx4 %4, %24, off offset:128\n\t"
+            "global_load_dwordx4 %5, %24, off offset:160\n\t"
+            "global_load_dwordx4 %6, %24, off offset:192\n\t"
+            "global_load_dwordx4 %7, %24, off offset:224\n\t"
+            "global_load_dwordx4 %8, %24, off offset:256\n\t"
+            "global_load_dwordx4 %9, %24, off offset:288\n\t"
+            "global_load_dwordx4 %10, %24, off offset:320\n\t"
+            "global_load_dwordx4 %11, %24, off offset:352\n\t"
+            "global_load_dwordx4 %12, %25, off\n\t"
+            "global_load_dwordx4 %13, %25, off offset:32\n\t"
+            "global_load_dwordx4 %14, %25, off offset:64\n\t"
+            "global_load_dwordx4 %15, %25, off offset:96\n\t"
+            "global_load_dwordx4 %16, %25, off offset:128\n\t"
+            "global_load_dwordx4 %17, %25, off offset:160\n\t"
+            "global_load_dwordx4 %18, %25, off offset:192\n\t"
+            "global_load_dwordx4 %19, %25, off offset:224\n\t"
+            "global_load_dwordx4 %20, %25, off offset:256\n\t"
+            "global_load_dwordx4 %21, %25, off offset:288\n\t"
+            "global_load_dwordx4 %22, %25, off offset:320\n\t"
+            "global_load_dwordx4 %23, %25, off offset:352\n\t"
+            "s_waitcnt vmcnt(0)"
+            : "=a"(qf[0][0]), "=a"(qf[0][1]), "=a"(qf[0][2]), "=a"(qf[0][3]), "=a"(qf[0][4]),
+              "=a"(qf[0][5]), "=a"(qf[0][6]), "=a"(qf[0][7]), "=a"(qf[0][8]), "=a"(qf[0][9]),
+              "=a"(qf[0][10]), "=a"(qf[0][11]), "=a"(qf[1][0]), "=a"(qf[1][1]), "=a"(qf[1][2]),
+              "=a"(qf[1][3]), "=a"(qf[1][4]), "=a"(qf[1][5]), "=a"(qf[1][6]), "=a"(qf[1][7]),
+              "=a"(qf[1][8]), "=a"(qf[1][9]), "=a"(qf[1][10]), "=a"(qf[1][11])
+            : "v"(p[0]), "v"(p[1]) : "memory");
     }
 }
 
@@ -613,7 +688,7 @@ __device__ __forceinline__ void static_range(F&& f) {
 // part shared by all heads k_rope [rows][64], the key layout of the MLA models.
 template <int DQK, int DV, int NB, int KVM>
 __global__ __attribute__((amdgpu_flat_work_group_size(NTHREADS, NTHREADS), amdgpu_waves_per_eu(3 - NB, 3 - NB)))
-void attn_fwd_kernel(AttnArgs a, GroupTable) {
+void attn_fwd_kernel(AttnArgs args, GroupTable) {
     constexpr bool PAGED = KVM == KV_PAGED;
     constexpr bool ROPE = KVM == KV_ROPE;
     static_assert(!ROPE || DQK == 192, "the split key layout is 128 + 64 dims");
@@ -622,6 +697,10 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
     constexpr int KS = T::KS;
     constexpr int DB = T::DB;
     constexpr int WROWS = 32 * NB;  // query rows per wave
+    // LDS fragment prefetch distances (in fragments) of the K and V^T operands; shorter
+    // where the 256 registers of a 32-row wave would not hold them beside 192 dims
+    constexpr int K_AHEAD = NB == 1 && DQK == 192 ? 2 : 3;
+    constexpr int V_AHEAD = NB == 1 && DQK == 192 ? 1 : 2;
     typedef Schedule<T::NQK, T::NPV, DB, NB> SchedFull;
     typedef Schedule<0, T::NPV, DB, NB> SchedLast;
     static_assert(SchedFull().valid() && SchedLast().valid(), "tile schedule breaks a dependency");
@@ -636,27 +715,32 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
         return table ? (uint64_t)(uintptr_t)table
                      : (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(AttnArgs);
     };
-    const int gidx = find_entry(group_base(a.groups), sizeof(LaunchGroup), a.num_groups, (int)blockIdx.x);
-    const_group_t* const grp = const_ptr<const_group_t>(group_base(a.groups)) + gidx;
-    const int slots = grp->slots, pieces = grp->pieces;
-    int slot, h;
-    const int seg_tiles = grp->tiles;
-    const bool paired = slots != seg_tiles;
-    work_coords((int)blockIdx.x - grp->wg0, slots, a.head_groups * pieces, paired, a.xcd_remap != 0, slot, h);
-    int piece = 0, piece_kb = 0, piece_ke = INT32_MAX;
-    if (pieces > 1) {
-        const int hg = h / pieces;
-        piece = pieces - 1 - (h - hg * pieces);  // the last piece is the longest: first
-        h = hg;
-        piece_kb = piece_begin(grp->prefix, pieces, piece);
-        if (piece + 1 < pieces) piece_ke = piece_begin(grp->prefix, pieces, piece + 1);
-    }
-    h *= a.pack;  // the tile's first head
+    const int gidx0 = find_entry(group_base(args.groups), sizeof(LaunchGroup), args.num_groups, (int)blockIdx.x);
     auto row_token = [](int r, int magic) { return (int)((uint32_t)r * (uint32_t)magic >> 16); };
     // A slot holds up to two tiles of the segment: the first runs its key range
     // ascending, its partner from the other end (if any) descending.
 #pragma nounroll
     for (int sub = 0; sub < 2; ++sub) {
+        // Everything about the tile is worked out again for the second one, from the
+        // kernel arguments on (the empty asm hides that it was known), so none of it
+        // occupies scalar registers across the key loop.
+        int gidx = gidx0;
+        const_args_t* ap = (const_args_t*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(gidx), "+s"(ap));
+        const_args_t& a = *ap;
+        const_group_t* const grp = const_ptr<const_group_t>(group_base(a.groups)) + gidx;
+        const int slots = grp->slots, seg_tiles = grp->tiles, pieces = grp->pieces;
+        const bool paired = slots != seg_tiles;
+        int slot, hg, piece = 0, piece_kb = 0, piece_ke = INT32_MAX;  // hg: head group
+        work_coords((int)blockIdx.x - grp->wg0, slots, a.head_groups * pieces, paired, a.xcd_remap != 0, slot, hg);
+        if (pieces > 1) {
+            const int hp = hg;
+            hg = hp / pieces;
+            piece = pieces - 1 - (hp - hg * pieces);  // the last piece is the longest: first
+            piece_kb = piece_begin(grp->prefix, pieces, piece);
+            if (piece + 1 < pieces) piece_ke = piece_begin(grp->prefix, pieces, piece + 1);
+        }
+        const int h = hg * a.pack;  // the tile's first head
         const int ti = sub == 0 ? slot : seg_tiles - 1 - slot;
         if (sub == 1 && (!paired || ti == slot)) break;
         const int t_row0 = ti * a.tile_tokens;  // the tile's first token in the segment
@@ -667,11 +751,14 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
         it.key_begin = piece_kb;
         it.key_end = min(piece_ke, it.pos0 + it.nrows);
         const int64_t kv_start = grp->kv_start;
+        // where the results go: the tile's first chunk row, or ~ its first partial row
+        const int out_row0 = grp->part0 < 0 ? it.row0 : ~(grp->part0 + piece * grp->len + t_row0);
         // every wave is done with the LDS tiles of the slot's previous tile before
         // this tile's first copies overwrite them
         lds_barrier();
-        const int hk = h / a.group;
-        const int tid = threadIdx.x;
+        const int hk = a.pack == a.group ? hg : h / a.group;
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));  // nor any lane's offsets vector registers
         const int lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: LDS bases stay scalar
         const int lr = lane & 31;
@@ -712,6 +799,7 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
         // are never stored), so every load stays inside q.
         const int tile_rows = it.nrows * a.pack;  // at most BM
         bf16x8 qf[NB][KS];
+        const u16* qp[NB];
         int qlim[NB];   // last key position the row may see, minus lg*4 (see masking)
         bool qvalid[NB];
 #pragma unroll
@@ -721,10 +809,8 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
             const int r = min(rloc, tile_rows - 1);
             const int tok = row_token(r, a.pack_magic);
             qlim[nb] = min(it.pos0 + tok, ke - 1) - lg * 4;
-            const u16* qp = a.q + (int64_t)(it.row0 + tok) * a.q_st + (int64_t)(h + r - tok * a.pack) * a.q_sh + lg * 8;
-            load_q_agpr<KS>(qf[nb], qp);
+            qp[nb] = a.q + (int64_t)(it.row0 + tok) * a.q_st + (int64_t)(h + r - tok * a.pack) * a.q_sh + lg * 8;
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         const int wave_first = it.pos0 + row_token(wave * WROWS, a.pack_magic);
 
         // Global->LDS copy of one tile through a buffer resource whose base is the
@@ -802,6 +888,10 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
             issue_v(std::integral_constant<int, 0>(), kt_first);
             if (ntiles > 1) issue_k(std::integral_constant<int, 1>(), kt_first + dkt);
         }
+        // The query rows travel with the first copies: one latency (4 to 5 thousand
+        // cycles on a busy chip) where Q first and then the copies cost 1.5 to 2
+        // thousand more.
+        load_q_agpr<KS, NB>(qf, qp);
 
         // Per-lane LDS byte offsets; the rest of each address is an immediate.
         // K (A operand of S^T): row mb*32+lr, logical granule ks*2+lg; row & 15 and
@@ -826,10 +916,15 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
         const int tq = lane >> 4, tj = lane & 15;
         const int tr_key = 4 * (tq >> 1) + (tj >> 2);
         const int tr_col = 16 * (tq & 1) + 4 * (tj & 3);
-        int v_off[DB];
+        // The LDS offset of the V buffers is part of the register (the empty asm keeps it
+        // there): added to an immediate it would pass the 16 bits of one at dqk = 192.
+        uint32_t v_off[DB];
 #pragma unroll
-        for (int d = 0; d < DB; ++d)
-            v_off[d] = tr_key * (T::VGR * 16) + vswz<T::VGR>(tr_key, d * 4 + (tr_col >> 3)) * 16 + (tr_col & 7) * 2;
+        for (int d = 0; d < DB; ++d) {
+            v_off[d] = (uint32_t)(uintptr_t)(lds_void_t*)vbuf0 + tr_key * (T::VGR * 16) +
+                       vswz<T::VGR>(tr_key, d * 4 + (tr_col >> 3)) * 16 + (tr_col & 7) * 2;
+            asm volatile("" : "+v"(v_off[d]));
+        }
 
         float m_run[NB];   // max used by exp2 (log2 units), refreshed lazily
         float l_part[NB];  // this lane's share of the softmax denominator
@@ -858,12 +953,13 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
                 return __builtin_bit_cast(bf16x8, raw);
             }
         };
-        auto load_vfrag = [&](const char* vt, int mb, int hh, int d) -> bf16x8 {
+        typedef __attribute__((address_space(3))) char lds_char_t;
+        auto load_vfrag = [&](int vt, int mb, int hh, int d) -> bf16x8 {  // vt: byte offset of the V buffer
             bf16x8 af;
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
-                const char* addr = vt + (mb * 32 + hh * 16 + half * 8) * T::VGR * 16 + v_off[d];
-                const i16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(addr));
+                lds_char_t* addr = (lds_char_t*)(uintptr_t)v_off[d] + (vt + (mb * 32 + hh * 16 + half * 8) * T::VGR * 16);
+                const i16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)addr);
                 const bf16x4 rb = __builtin_bit_cast(bf16x4, r);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) af[half * 4 + j] = rb[j];
@@ -915,13 +1011,16 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
             }
         }
 
+        float scale_log2 = a.scale_log2;
+        asm volatile("" : "+s"(scale_log2));  // held in a register, not read again every step
+
         // One key tile: mask S(t) if needed, then the scheduled mix of S(t+1)
         // MFMAs, the softmax of S(t) and the O^T += V^T P^T MFMAs of tile t.
         auto step = [&](auto P, auto HAS_NEXT, int t, f32x16 (&s_cur)[2][NB], f32x16 (&s_nxt)[2][NB]) {
             constexpr int par = decltype(P)::value;
             constexpr bool has_next = decltype(HAS_NEXT)::value;
             const char* kt_nxt = kbuf0 + (1 - par) * T::K_BYTES;
-            const char* vt_cur = vbuf0 + par * T::V_BYTES;
+            constexpr int vt_cur = par * T::V_BYTES;
             const int kt = kt_first + t * dkt;
             wait_vmcnt<0>();
             lds_barrier();  // K(t+1), V(t) are in LDS; every wave is done with K(t) and V(t-1)
@@ -1015,7 +1114,7 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
                 } else if constexpr (k < A::EXP) {
                     constexpr int nb = k - A::MAXF;
                     const float m =
-                        lane_swap32_max(max3f(mx[nb][0], mx[nb][1], max2f(mx[nb][2], mx[nb][3]))) * a.scale_log2;
+                        lane_swap32_max(max3f(mx[nb][0], mx[nb][1], max2f(mx[nb][2], mx[nb][3]))) * scale_log2;
                     // per-lane decision: the exps of this row wait only for VALU work;
                     // the wave-wide vote happens once, at the rescale check
                     refresh[nb] = m > m_run[nb] + LAZY_TAU;
@@ -1029,7 +1128,7 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
                     constexpr int e = k - A::EXP;
                     constexpr int u = e >> 3, j = e & 7;
                     constexpr int mb = u / (2 * NB), hh = (u / NB) & 1, nb = u % NB;
-                    const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s_cur[mb][nb][hh * 8 + j], a.scale_log2, -m_use[nb]));
+                    const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s_cur[mb][nb][hh * 8 + j], scale_log2, -m_use[nb]));
                     lsum[nb][j & 1] += pv;
                     if constexpr ((j & 1) == 0) {
                         pprev = pv;
@@ -1063,7 +1162,8 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
                         bool any = false;
 #pragma unroll
                         for (int nb = 0; nb < NB; ++nb) any = any || refresh[nb];
-                        if (__builtin_amdgcn_ballot_w64(any) != 0) {
+                        // nothing to rescale on the first tile: O is zero
+                        if (t > 0 && __builtin_amdgcn_ballot_w64(any) != 0) {
                             // rare: rescale the AGPR accumulators 16 at a time, so the
                             // branch needs only a few temporary VGPRs (alpha = 1 in the
                             // lanes whose reference did not move)
@@ -1131,7 +1231,6 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
             typedef std::integral_constant<bool, true> NX;
             typedef std::integral_constant<bool, false> LAST;
             f32x16 s_a[2][NB], s_b[2][NB];
-            wait_vmcnt<0>();
             lds_barrier();
             qk_all(kbuf0, s_a);
             mfma_drain();
@@ -1154,21 +1253,20 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
         // The arguments only the epilogue needs are read again from the kernel
         // argument segment (the empty asm hides that they were read before), so
         // they do not occupy scalar registers across the key loop.
-        const AttnArgs* ka = (const AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+        const_args_t* ka = (const_args_t*)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(ka));
-        const_group_t* const g2 = const_ptr<const_group_t>(group_base(ka->groups)) + gidx;
-        const int part0 = g2->part0;
-        const int row0 = (part0 >= 0 ? part0 + piece * g2->len : g2->row0) + t_row0;
+        const bool partial = out_row0 < 0;
+        const int row0 = partial ? ~out_row0 : out_row0;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const float l_tot = lane_swap32_add(l_part[nb]);
             const float inv_l = l_tot > 0.f ? 1.f / l_tot : 0.f;
             const float lse_val = l_tot > 0.f ? (m_run[nb] + __log2f(l_tot)) * 0.69314718055994531f : -INFINITY;
-            if (!qvalid[nb]) continue;
             const int rloc = wave * WROWS + nb * 32 + lr;
             const int tok = row_token(rloc, ka->pack_magic);
             const int row = row0 + tok, hh = h + rloc - tok * ka->pack;
-            if (part0 >= 0) {
+            if (partial) {
+                if (!qvalid[nb]) continue;
                 const int64_t prow = (int64_t)row * ka->num_heads + hh;
                 float* po = ka->part_o + prow * DV;
 #pragma unroll
@@ -1181,17 +1279,29 @@ void attn_fwd_kernel(AttnArgs a, GroupTable) {
                     }
                 if (lg == 0) ka->part_lse[prow] = lse_val;
             } else {
-                u16* op = ka->out + (int64_t)row * ka->o_st + (int64_t)hh * ka->o_sh;
+                // A lane holds columns c*8 + lg*4 .. +3 of its row, its partner (lane ^ 32)
+                // the other four of each eight: for two values of c they exchange halves, and
+                // each stores 16 bytes. Stores of 8 bytes took twice as many instructions, each
+                // touching as many lines.
+                u16* op = ka->out + (int64_t)row * ka->o_st + (int64_t)hh * ka->o_sh + lg * 8;
 #pragma unroll
                 for (int d = 0; d < DB; ++d)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        bf16x4 w;
+                    for (int c = 0; c < 4; c += 2) {
+                        u32x2 w[2];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) w[j] = (__bf16)(o[d][nb][c * 4 + j] * inv_l);
-                        *(bf16x4*)(op + d * 32 + c * 8 + lg * 4) = w;
+                        for (int e = 0; e < 2; ++e) {
+                            bf16x4 x;
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) x[j] = (__bf16)(o[d][nb][(c + e) * 4 + j] * inv_l);
+                            w[e] = __builtin_bit_cast(u32x2, x);
+                        }
+                        const auto lo = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+                        const auto hi = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+                        const u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
+                        if (qvalid[nb]) *(u32x4*)(op + d * 32 + c * 8) = v;
                     }
-                if (lg == 0 && ka->lse) ka->lse[(int64_t)hh * ka->lse_sh + row] = lse_val;
+                if (lg == 0 && qvalid[nb] && ka->lse) ka->lse[(int64_t)hh * ka->lse_sh + row] = lse_val;
             }
         }
     }  // slot tiles
@@ -1427,10 +1537,10 @@ bool supported_dims(int dqk, int dv) {
 // wave. A chunk of at most two 256-row workgroups per CU and short key ranges (at
 // most 8192 keys per tile on average) takes the 128-row tiles (NB = 1, two
 // workgroups per CU), which even out the unequal key ranges of the diagonal tiles;
-// others take what the launch model below finds faster. With dqk = 192 the 32-row
-// waves spill a few registers, so they run only segments that would leave a 256-row
-// tile at least half empty: two workgroups a CU stream distinct keys at 5.9 TB/s
-// where one reaches 4.0. VPP_NB overrides, for tuning.
+// others take what the launch model below finds faster. With dqk = 192 a few whole
+// 256-row tiles keep them; otherwise the model chooses too: the 128-row tiles halve
+// what a short segment leaves empty, and two workgroups a CU stream distinct keys at
+// 5.9 TB/s where one reaches 4.0. VPP_NB overrides, for tuning.
 bool small_chunk(const vpp_chunk_attn_config_t& c, int64_t tiles256, double mean_keys256) {
     return c.head_dim_qk <= 128 && tiles256 * c.num_q_heads <= 2 * 256 && mean_keys256 <= 8192.0;
 }
@@ -1438,9 +1548,9 @@ int forced_nb() {
     const char* e = getenv("VPP_NB");
     return e && (atoi(e) == 1 || atoi(e) == 2) ? atoi(e) : 0;
 }
-int allowed_nb(const vpp_chunk_attn_config_t& c, bool small, int64_t max_rows) {
+int allowed_nb(const vpp_chunk_attn_config_t& c, bool small, int64_t tiles256, int64_t max_rows) {
     if (forced_nb()) return forced_nb();
-    if (c.head_dim_qk > 128) return max_rows <= 128 ? 3 : 2;
+    if (c.head_dim_qk > 128) return max_rows <= 128 || tiles256 * c.num_q_heads > 64 ? 3 : 2;
     return small ? 1 : 3;
 }
 
@@ -1518,19 +1628,25 @@ int64_t longest_slot(const SegPlan& s, int tt, int32_t begin, int32_t end) {
 struct LaunchModel {
     int heads, pack, dqk, dv;
 
-    // One 64-key step of a workgroup takes `few` us while few of them run. The chip as
-    // a whole finishes at most `rate` steps a us, held by power: past few * rate
-    // workgroups (three quarters of the CUs at dqk = 192) more of them in flight only
-    // slow each other down.
-    struct Speed { double few, rate; };
+    // One 64-key step of a workgroup takes `few` us while few of them run and `full` us
+    // with every place taken: one 256-row workgroup a CU, or two of 128 rows. In
+    // between the chip is held by power, which grows with the cube of its clock: 192 of
+    // 256 places busy step 1.1 times as fast as all of them, not 1.33 times.
+    struct Speed { double few, full; };
     Speed speed(int nb) const {
-        static const Speed table[2][3] = {{{0.63, 427.0}, {0.83, 277.0}, {1.20, 213.0}},
-                                          {{1.03, 233.0}, {1.30, 149.0}, {1.65, 125.0}}};
+        static const Speed table[2][3] = {{{0.64, 1.22}, {0.84, 1.85}, {1.08, 2.15}},
+                                          {{1.03, 1.20}, {1.31, 1.72}, {1.52, 2.04}}};
         return table[nb - 1][dqk == 64 ? 0 : dqk == 128 ? 1 : 2];
+    }
+    // a step with `wgs` workgroups in flight
+    static double step(const Speed& v, int nb, double wgs) {
+        if (nb == 2) return std::max(v.few, v.full * cbrt(wgs / NUM_CU));
+        if (wgs <= NUM_CU) return std::max(v.few, 1.17 * v.few * cbrt(wgs / NUM_CU));
+        return v.full * cbrt(wgs / (2 * NUM_CU));  // while any CU holds two, those set the pace
     }
     // What a tile costs beside its steps, in steps: Q load, pipeline fill, first and
     // last step, store. Two 128-row workgroups a CU hide much of each other's.
-    double tile(int nb) const { return nb == 1 ? 2.5 : 5.0; }
+    double tile(int nb) const { return nb == 1 ? 2.0 : 4.0; }
     // The rate at which workgroups stream distinct keys, one or two in flight per CU:
     // it holds back the steps of segments with few tiles.
     double stream(int nb) const { return nb == 1 ? 5.5e6 : 3.8e6; }  // bytes per us
@@ -1539,13 +1655,13 @@ struct LaunchModel {
     // Time of the merge of part_rows partial rows: a launch, and the partials written
     // and read back.
     double merge(int64_t part_rows) const {
-        return part_rows == 0 ? 0.0 : 5.0 + 2.0 * (double)part_rows * heads * (4.0 * dv + 4.0) / 5.0e6;
+        return part_rows == 0 ? 0.0 : 4.0 + 2.0 * (double)part_rows * heads * (4.0 * dv + 4.0) / 5.0e6;
     }
 
     // Time of a launch of `segs` (longest slots first): one XCD's share of each group
     // (work_coords), placed in order on whichever of its workgroup places frees first.
     // All places progress alike, so the schedule is found in steps and then put on the
-    // clock. While any CU holds two 128-row workgroups those two set the pace.
+    // clock.
     double launch(const std::vector<SegPlan>& segs, int nb, int tt, std::vector<double>& lanes) const {
         const int64_t groups = heads / pack;
         const int places = NUM_CU / NXCD * (3 - nb);
@@ -1603,12 +1719,12 @@ struct LaunchModel {
         double steps = 0.0;
         for (double l : lanes) steps += l * NXCD;
         std::sort(lanes.begin(), lanes.end());
-        Speed v = speed(nb);
-        v.rate = std::min(v.rate, stream(nb) * steps / bytes);
+        const Speed v = speed(nb);
+        const double stream_step = bytes / steps / stream(nb);  // us a step of each workgroup
         double t = 0.0, at = 0.0;
         for (int i = 0; i < places; ++i) {
-            const int active = places - i > NUM_CU / NXCD ? places : places - i;
-            t += (lanes[(size_t)i] - at) * std::max(v.few, (double)active * NXCD / v.rate);
+            const double wgs = (double)(places - i) * NXCD;
+            t += (lanes[(size_t)i] - at) * std::max(step(v, nb, wgs), wgs * stream_step);
             at = lanes[(size_t)i];
         }
         return t;
@@ -1673,7 +1789,7 @@ Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPla
             bytes += (double)groups * ((double)s.prefix + s.len) * (c.head_dim_qk + c.head_dim_v) * 2.0;
         }
         const double even = steps / (LaunchModel::NUM_CU * (3 - nb));
-        const double bound = std::max(steps / model.speed(nb).rate, bytes / model.stream(nb));
+        const double bound = std::max(even * model.speed(nb).full, bytes / model.stream(nb));
         for (int paired = 1; paired >= 0; --paired) {
             x.segs = segs;
             for (SegPlan& s : x.segs) {
@@ -1682,7 +1798,7 @@ Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPla
                 s.pieces = fixed > 1 ? (int)std::min<int64_t>(fixed, std::max(1, s.prefix / BN)) : 1;
             }
             consider(paired != 0, false);
-            if (fixed || best.t < 1.08 * bound) continue;
+            if (fixed || best.t < 1.04 * bound) continue;
             double last_t = 1e30;
             for (double f : {2.0, 1.0, 0.7, 0.5, 0.35, 0.25, 0.17, 0.12}) {
                 const double target = std::max(even * f, 4.0);  // steps of a workgroup
@@ -1696,7 +1812,7 @@ Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPla
                 }
                 if (!split) continue;
                 consider(paired != 0, true);
-                if (target <= 4.0 || (x.t > last_t && x.t > 1.1 * best.t) || best.t < 1.08 * bound) break;
+                if (target <= 4.0 || (x.t > last_t && x.t > 1.1 * best.t) || best.t < 1.04 * bound) break;
                 last_t = x.t;
             }
         }
@@ -1842,7 +1958,7 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
         }
         if (!segs.empty()) {
             const bool small = small_chunk(c, tiles256, keys256 / tiles256);
-            const int nb_mask = allowed_nb(c, small, max_rows);
+            const int nb_mask = allowed_nb(c, small, tiles256, max_rows);
             plan = choose_plan(c, segs, nb_mask, pack, SIZE_MAX);
             // a chunk that one-head tiles in pairs would keep within the scratch of
             // run_noalloc stays within it
