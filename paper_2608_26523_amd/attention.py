@@ -6,7 +6,9 @@ passes raw pointers and element strides to ``vpp_chunk_attn_plan`` /
 same without a workspace), ``vpp_chunk_attn_run_paged`` (paged cache) or
 ``vpp_chunk_attn_run_mla`` (keys split into per-head and shared parts);
 ``kv_append_paged`` wraps ``vpp_kv_append_paged``. Nothing here does arithmetic
-of its own.
+of its own. A call with plain tensors on the current stream goes through the
+native extension (``binding.load_torch``), which makes the same checks; what it
+does not take comes back before any device work and is done, or refused, here.
 """
 from __future__ import annotations
 
@@ -30,7 +32,7 @@ class ChunkAttention:
     def __init__(self, num_q_heads: int, num_kv_heads: int, head_dim_qk: int, head_dim_v: int,
                  max_chunk_tokens: int, max_kv_len: int, max_segments: int = 1024,
                  num_splits: int = -1, softmax_scale: float = 0.0, device=None):
-        B.load()
+        ext = B.load_torch()
         self.cfg = B.Config(num_q_heads=num_q_heads, num_kv_heads=num_kv_heads,
                             head_dim_qk=head_dim_qk, head_dim_v=head_dim_v,
                             softmax_scale=softmax_scale, causal=1,
@@ -40,6 +42,7 @@ class ChunkAttention:
         if dev.type != "cuda":
             raise ValueError("the workspace must be on a GPU, not %s" % dev)
         self.device = dev if dev.index is not None else torch.device("cuda", torch.cuda.current_device())
+        self._native = ext.Caller(num_q_heads, num_kv_heads, head_dim_qk, head_dim_v, self.device.index)
         self._plan: Optional[int] = None
         self._ws: Optional[torch.Tensor] = None
         self.workspace_bytes = 0
@@ -61,6 +64,7 @@ class ChunkAttention:
         if self._ws is None or self._ws.numel() < ws:
             self._ws = torch.empty(ws, dtype=torch.uint8, device=self.device)
         self.tokens = int(cu_q[-1])
+        self._native.set_plan(h, self.tokens, self.max_row, len(self.seg_rows), max(self.seg_rows or [0]))
         return B.vpp_chunk_attn_plan_info(h)
 
     def info(self):
@@ -70,6 +74,13 @@ class ChunkAttention:
         return B.vpp_chunk_attn_plan_items(self._plan)
 
     # -- running ------------------------------------------------------------
+    @staticmethod
+    def _done(status: int, where: str) -> bool:
+        """Whether the native extension made the call (it returns -1 for what it does not take)."""
+        if status > 0:
+            raise B.VppError(status, where)
+        return status == 0
+
     @staticmethod
     def _check(t: torch.Tensor, name: str, dtype, ndim: int):
         if t.dtype != dtype:
@@ -149,6 +160,9 @@ class ChunkAttention:
         element [h, r] is chunk row r of head h (e.g. a column slice of a
         [Hq, seq] tensor), or None.
         """
+        if stream is None and self._done(self._native.run(q, k_cache, v_cache, out, lse, self._ws),
+                                         "vpp_chunk_attn_run"):
+            return out, lse
         out, lse_ptr, lse_sh, new_out = self._io(q, out, lse)
         self._check_cache(k_cache, v_cache)
         s = self._stream(stream, new_out)
@@ -170,6 +184,9 @@ class ChunkAttention:
         are refused; calls that overlap on one GPU share its scratch and race."""
         if out is None:
             raise ValueError("run_noalloc allocates nothing: pass out")
+        if stream is None and self._done(self._native.run_noalloc(q, k_cache, v_cache, out, lse),
+                                         "vpp_chunk_attn_run_noalloc"):
+            return out, lse
         out, lse_ptr, lse_sh, _ = self._io(q, out, lse)
         self._check_cache(k_cache, v_cache)
         s = stream if stream is not None else torch.cuda.current_stream(self.device)
@@ -190,6 +207,9 @@ class ChunkAttention:
                 stream: Optional[torch.cuda.Stream] = None):
         """Like ``run`` with the keys split as in the MLA models: k_nope [rows, Hkv, 128] per
         head and k_rope [rows, 64] shared by all heads (head dims (192, 128) only)."""
+        if stream is None and self._done(self._native.run_mla(q, k_nope, k_rope, v_cache, out, lse, self._ws),
+                                         "vpp_chunk_attn_run_mla"):
+            return out, lse
         out, lse_ptr, lse_sh, new_out = self._io(q, out, lse)
         c = self.cfg
         if c.head_dim_qk != 192 or c.head_dim_v != 128:
@@ -222,6 +242,9 @@ class ChunkAttention:
         """Like ``run`` over a paged cache: k_pages [pages, page_size, Hkv, dqk], v_pages
         [pages, page_size, Hkv, dv] bf16; block_table int32 [segments, pages_per_row] on the
         device (row s: the pages of segment s's request, in cache-row order)."""
+        if stream is None and self._done(self._native.run_paged(q, k_pages, v_pages, block_table, out, lse, self._ws),
+                                         "vpp_chunk_attn_run_paged"):
+            return out, lse
         out, lse_ptr, lse_sh, new_out = self._io(q, out, lse)
         c = self.cfg
         self._check(k_pages, "k_pages", torch.bfloat16, 4)
@@ -257,6 +280,7 @@ class ChunkAttention:
 
     def close(self):
         if self._plan is not None:
+            self._native.set_plan(0, 0, 0, 0, 0)
             B.vpp_chunk_attn_destroy(self._plan)
             self._plan = None
         self._ws = None
@@ -273,6 +297,9 @@ def kv_append_paged(k_new: torch.Tensor, v_new: torch.Tensor, k_pages: torch.Ten
                     stream: Optional[torch.cuda.Stream] = None) -> None:
     """Write k_new [tokens, Hkv, dqk] and v_new [tokens, Hkv, dv] (bf16) into the paged caches
     at slot_mapping [tokens] (int64, on the GPU; slot = page * page_size + row, -1 skips)."""
+    if stream is None and ChunkAttention._done(B.load_torch().append(k_new, v_new, k_pages, v_pages, slot_mapping),
+                                               "vpp_kv_append_paged"):
+        return
     for t, name in ((k_new, "k_new"), (v_new, "v_new")):
         ChunkAttention._check(t, name, torch.bfloat16, 3)
     for t, name in ((k_pages, "k_pages"), (v_pages, "v_pages")):

@@ -13,6 +13,7 @@ from typing import Optional, Sequence
 import numpy as np
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libvpp_chunk_attn.so")
+TORCH_LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "vpp_torch.so")
 
 VPP_OK = 0
 VPP_ERR_INVALID_ARG = 1
@@ -116,6 +117,31 @@ def load(path: Optional[str] = None):
     if path == LIB_PATH:
         _lib = lib
     return lib
+
+
+_torch_ext = None
+
+
+def load_torch():
+    """The extension that makes the calls on torch tensors, bound to this library; raise if it
+    has not been built."""
+    global _torch_ext
+    if _torch_ext is None:
+        lib = load()
+        if not os.path.exists(TORCH_LIB_PATH):
+            raise ImportError("extension %s is missing: run __graft_entry__.build() "
+                              "(or python -m paper_2608_26523_amd.build)" % TORCH_LIB_PATH)
+        import importlib.util
+
+        import torch  # noqa: F401  (the extension's own libraries)
+        spec = importlib.util.spec_from_file_location("vpp_torch", TORCH_LIB_PATH)
+        ext = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(ext)
+        ext.bind(*(ctypes.cast(fn, ctypes.c_void_p).value
+                   for fn in (lib.vpp_chunk_attn_run, lib.vpp_chunk_attn_run_noalloc, lib.vpp_chunk_attn_run_mla,
+                              lib.vpp_chunk_attn_run_paged, lib.vpp_kv_append_paged)))
+        _torch_ext = ext
+    return _torch_ext
 
 
 def vpp_status_str(status: int) -> str:

@@ -1,6 +1,7 @@
 """Build the native libraries in-tree: the HIP attention library (hipcc for gfx950) into
-paper_2608_26523_amd/libvpp_chunk_attn.so, and the host-only schedule model (g++) into
-paper_2608_26523_amd/libvpp_sched.so."""
+paper_2608_26523_amd/libvpp_chunk_attn.so, the host-only schedule model (g++) into
+paper_2608_26523_amd/libvpp_sched.so, and the extension that calls the attention library on
+torch tensors (g++) into paper_2608_26523_amd/vpp_torch.so."""
 from __future__ import annotations
 
 import os
@@ -14,6 +15,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libvpp_chunk_attn.so")
 SCHED_SRC = os.path.join(PKG, "csrc", "vpp_sched.cpp")
 SCHED_LIB = os.path.join(PKG, "libvpp_sched.so")
+TORCH_SRC = os.path.join(PKG, "csrc", "vpp_torch.cpp")
+TORCH_LIB = os.path.join(PKG, "vpp_torch.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-shared",
@@ -70,6 +73,30 @@ def build_sched(out: str = SCHED_LIB) -> str:
     return out
 
 
+def build_torch(out: str = TORCH_LIB) -> str:
+    """The extension module is host C++ against torch's headers; it runs no kernel of its own."""
+    import sysconfig
+
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    tlib = os.path.join(troot, "lib")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    tmp = out + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", INCLUDE, "-isystem", os.path.join(troot, "include"),
+           "-isystem", os.path.join(troot, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"),
+           "-o", tmp, TORCH_SRC, "-L", tlib, "-Wl,-rpath," + tlib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch",
+           "-ltorch_python"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
+    os.replace(tmp, out)
+    return out
+
+
 if __name__ == "__main__":
     print(build(quiet=False))
     print(build_sched())
+    print(build_torch())
