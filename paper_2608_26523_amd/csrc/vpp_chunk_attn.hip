@@ -100,17 +100,24 @@ __device__ __forceinline__ i32x4 make_rsrc(const void* base, int32_t bytes) {
 // inserts no wait for them in front of later LDS reads of other buffers; the
 // kernel waits for them itself (vmcnt) before the barrier that publishes the
 // buffer they fill. Nothing else in the kernel keeps a value in M0.
-template <int OFF>
+// NT: non-temporal, for tiles that no other workgroup reads (see Launch::nt).
+template <int OFF, bool NT>
 __device__ __forceinline__ void copy16_to_lds(const i32x4& rsrc, uint32_t lds_base, uint32_t voff) {
     // M0 = lds_base + OFF: one live SGPR for every copy of the kernel.
     // The scalar add also writes SCC: without the clobber the compiler may
     // place a copy between the two halves of a 64-bit scalar add and the high
     // half then adds the copy's carry instead of its own (an address 4 GiB off
     // whenever the low half wraps).
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :
-                 : "s"(lds_base), "v"(voff), "s"(rsrc), "i"(OFF)
-                 : "memory", "scc");
+    if constexpr (NT)
+        asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+                     :
+                     : "s"(lds_base), "v"(voff), "s"(rsrc), "i"(OFF)
+                     : "memory", "scc");
+    else
+        asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                     :
+                     : "s"(lds_base), "v"(voff), "s"(rsrc), "i"(OFF)
+                     : "memory", "scc");
 }
 
 typedef vpp_chunk_attn_work_item_t WorkItem;
@@ -216,6 +223,13 @@ struct Launch {
     CombineArgs merge;
     CombineTable segs;
     int32_t nb, dqk;
+    // Whether most of the launch's key steps are of segments with one tile a head group,
+    // whose K/V tiles no other workgroup reads: their copies are then non-temporal
+    // (128-row tiles only, which such launches use). Single tokens behind 4K to 23K
+    // cached ones: 64 of 32/8 heads 635 -> 578 us, 16 of 16 MLA heads 194 -> 176; a
+    // serving step with a 480-row prompt piece 257 -> 233. Where tiles share their keys
+    // it costs 1.5 to 6 % (six short prompts 233 -> 247), the L2 keeping them too briefly.
+    bool nt;
     int64_t workgroups;
 };
 
@@ -686,7 +700,7 @@ __device__ __forceinline__ void static_range(F&& f) {
 // KV_PAGED: the same rows in pages reached through a block table; KV_ROPE
 // (dqk = 192 only): K split into a per-head part k_nope [rows][Hkv][128] and a
 // part shared by all heads k_rope [rows][64], the key layout of the MLA models.
-template <int DQK, int DV, int NB, int KVM>
+template <int DQK, int DV, int NB, int KVM, bool NT>
 __global__ __attribute__((amdgpu_flat_work_group_size(NTHREADS, NTHREADS), amdgpu_waves_per_eu(3 - NB, 3 - NB)))
 void attn_fwd_kernel(AttnArgs args, GroupTable) {
     constexpr bool PAGED = KVM == KV_PAGED;
@@ -864,15 +878,15 @@ void attn_fwd_kernel(AttnArgs args, GroupTable) {
             constexpr int t = decltype(TT)::value;
             if constexpr (ROPE && t >= NOPE_LOADS) {
                 constexpr int off = decltype(B)::value * T::K_BYTES + NOPE_BYTES + (t - NOPE_LOADS) * NWAVES * 1024;
-                copy16_to_lds<off>(rr, lds_wave, k_src[t]);
+                copy16_to_lds<off, NT>(rr, lds_wave, k_src[t]);
             } else {
                 constexpr int off = decltype(B)::value * T::K_BYTES + t * NWAVES * 1024;
-                copy16_to_lds<off>(r, lds_wave, k_src[t]);
+                copy16_to_lds<off, NT>(r, lds_wave, k_src[t]);
             }
         };
         auto load_v = [&](const i32x4& r, auto B, auto TT) {
             constexpr int off = 2 * T::K_BYTES + decltype(B)::value * T::V_BYTES + decltype(TT)::value * NWAVES * 1024;
-            copy16_to_lds<off>(r, lds_wave, v_src[decltype(TT)::value]);
+            copy16_to_lds<off, NT>(r, lds_wave, v_src[decltype(TT)::value]);
         };
         auto issue_k = [&](auto B, int kt) {
             const i32x4 r = k_rsrc(kt);
@@ -1402,16 +1416,23 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, CombineTabl
 
 [[maybe_unused]] size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-template <int DQK, int DV, int NB, int KVM>
-hipError_t launch(const Launch& l, hipStream_t stream) {
+template <int DQK, int DV, int NB, int KVM, bool NT>
+hipError_t launch_kernels(const Launch& l, hipStream_t stream) {
     if (l.workgroups <= 0) return hipSuccess;
     if (l.workgroups > (int64_t)INT32_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((attn_fwd_kernel<DQK, DV, NB, KVM>), dim3((unsigned)l.workgroups), dim3(NTHREADS), 0, stream,
+    hipLaunchKernelGGL((attn_fwd_kernel<DQK, DV, NB, KVM, NT>), dim3((unsigned)l.workgroups), dim3(NTHREADS), 0, stream,
                        l.a, l.groups);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || l.merge.blocks == 0) return e;
     hipLaunchKernelGGL((combine_kernel<DV>), dim3((unsigned)l.merge.blocks), dim3(256), 0, stream, l.merge, l.segs);
     return hipGetLastError();
+}
+
+template <int DQK, int DV, int NB, int KVM>
+hipError_t launch(const Launch& l, hipStream_t stream) {
+    if constexpr (NB == 1)
+        if (l.nt) return launch_kernels<DQK, DV, NB, KVM, true>(l, stream);
+    return launch_kernels<DQK, DV, NB, KVM, false>(l, stream);
 }
 
 template <int KVM>
@@ -1535,6 +1556,7 @@ struct vpp_chunk_attn_plan_s {
     int32_t num_splits = 1;
     int32_t nb = 2;  // 32-row query blocks per wave of the kernel variant the plan was made for
     int32_t pack = 1, tile_tokens = 256;
+    bool nt = false;
     int32_t tokens = 0;
     double pairs = 0.0;
     size_t table_bytes = 0;  // groups, then merges, where they exceed the kernel arguments; else 0
@@ -1670,7 +1692,7 @@ struct LaunchModel {
     double tile(int nb) const { return nb == 1 ? 2.0 : 4.0; }
     // The rate at which workgroups stream distinct keys, one or two in flight per CU:
     // it holds back the steps of segments with few tiles.
-    double stream(int nb) const { return nb == 1 ? 5.5e6 : 3.8e6; }  // bytes per us
+    double stream(int nb) const { return nb == 1 ? 6.0e6 : 3.8e6; }  // bytes per us
     static constexpr int NUM_CU = 256, NXCD = 8;
 
     // Time of the merge of part_rows partial rows: a launch, and the partials written
@@ -1964,6 +1986,7 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
     std::vector<CombineSeg> merges;
     double pairs = 0.0;
     int64_t ntiles = 0, nslots = 0, wgs = 0, part_rows = 0, blocks = 0;
+    double key_steps = 0.0, lone_steps = 0.0;  // per head group; of segments of one tile
     int nsplit = 1;
     try {
         std::vector<SegPlan> segs;
@@ -2009,6 +2032,9 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
             wgs += (int64_t)g.slots * s.pieces * (c.num_q_heads / pack);
             ntiles += s.tiles;
             nslots += s.slots();
+            const double keys = s.tiles * (s.prefix + 0.5 * s.len);
+            key_steps += keys;
+            if (s.tiles == 1) lone_steps += keys;
         }
     } catch (const std::bad_alloc&) {
         return VPP_ERR_NOMEM;
@@ -2024,6 +2050,7 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
     p->nb = nb;
     p->pack = pack;
     p->tile_tokens = tt;
+    p->nt = nb == 1 && lone_steps > 0.5 * key_steps;
     p->scale = c.softmax_scale > 0.f ? c.softmax_scale : (float)(1.0 / sqrt((double)c.head_dim_qk));
     p->segs.swap(plan.segs);
     p->groups.swap(groups);
@@ -2243,6 +2270,7 @@ vpp_status_t run_impl(vpp_chunk_attn_plan_t p, const void* q, int64_t q_st, int6
     memset(&l.merge, 0, sizeof l.merge);
     l.nb = p->nb;
     l.dqk = c.head_dim_qk;
+    l.nt = p->nt;
     l.workgroups = p->workgroups;
     AttnArgs& a = l.a;
     a.num_groups = (int32_t)p->groups.size();

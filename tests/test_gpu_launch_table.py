@@ -90,3 +90,45 @@ def test_pieces_and_merge(heads, dims, segs, splits):
     r, h = np.repeat(np.arange(tok), hq), np.tile(np.arange(hq), tok)
     rep = PA.compare(out, lse, r, h, ro.reshape(tok * hq, -1), rl.T.reshape(-1))
     assert rep.ok(), str(rep)
+
+
+# single tokens behind cached prefixes: one tile a head group, whose K/V copies are
+# non-temporal; contiguous against the oracle, paged and split keys against contiguous
+@pytest.mark.parametrize("heads,dims", [((4, 2), (64, 64)), ((32, 4), (128, 128)), ((6, 6), (192, 128))])
+def test_single_tokens(heads, dims):
+    from paper_2608_26523_amd.attention import ChunkAttention
+    (hq, hkv), (dqk, dv) = heads, dims
+    pre, page = [0, 63, 64, 700, 5000], 64
+    n = len(pre)
+    rows = [p + 1 for p in pre]
+    kvs = [int(x) for x in np.cumsum([0] + rows[:-1])]
+    cu = np.arange(n + 1)
+    T = sum(rows)
+    print("case:", heads, dims, flush=True)
+    q, k, v = _rand((n, hq, dqk), 1), _rand((T, hkv, dqk), 2), _rand((T, hkv, dv), 3)
+    if dqk == 192:
+        k[:, 1:, 128:] = k[:, :1, 128:]  # one shared part per row
+    attn = ChunkAttention(hq, hkv, dqk, dv, max_chunk_tokens=n, max_kv_len=T)
+    out, lse = PA.run_chunk(attn, q, k, v, cu, kvs, pre)
+    assert attn.info().block_m == 128
+    ro, rl = oracle.attention_full(q.cpu(), k.cpu(), v.cpu(), cu, kvs, pre)
+    r, h = np.repeat(np.arange(n), hq), np.tile(np.arange(hq), n)
+    rep = PA.compare(out, lse, r, h, ro.reshape(n * hq, -1), rl.T.reshape(-1))
+    assert rep.ok(), str(rep)
+    if dqk == 192:
+        out_s, _ = attn.run_mla(q, k[:, :, :128], k[:, 0, 128:], v)
+        assert torch.equal(out_s, out)
+    per = [-(-x // page) for x in rows]
+    table = torch.zeros((n, max(per)), dtype=torch.int32)
+    kp = torch.zeros((sum(per), page, hkv, dqk), dtype=torch.bfloat16, device=DEV)
+    vp = torch.zeros((sum(per), page, hkv, dv), dtype=torch.bfloat16, device=DEV)
+    at = 0
+    for s in range(n):
+        table[s, :per[s]] = torch.arange(at, at + per[s])
+        kp[at:at + per[s]].view(-1, hkv, dqk)[:rows[s]] = k[kvs[s]:kvs[s] + rows[s]]
+        vp[at:at + per[s]].view(-1, hkv, dv)[:rows[s]] = v[kvs[s]:kvs[s] + rows[s]]
+        at += per[s]
+    attn.plan(cu, [0] * n, pre)
+    out_p, _ = attn.run_paged(q, kp, vp, table.to(DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(out_p, out)
