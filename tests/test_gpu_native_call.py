@@ -178,3 +178,29 @@ def test_side_stream_and_closed_plan():
     attn.close()
     with pytest.raises(RuntimeError):
         attn.run(**args)
+
+
+def test_graph_replays_equal_eager():
+    """A chunk captured without a warm-up call (its launch table is in the kernel arguments) and
+    replayed on new contents of its buffers, a split plan's merge among it; eager work of the
+    same plan between the replays."""
+    from paper_2608_26523_amd.attention import ChunkAttention
+    hq, hkv, d, p, n = 4, 2, 128, 4000, 30
+    attn = ChunkAttention(hq, hkv, d, d, max_chunk_tokens=n, max_kv_len=p + n)
+    assert attn.plan([0, n], [0], [p]).num_splits > 1
+    q, k, v = _rand(n, hq, d), _rand(p + n, hkv, d, seed=1), _rand(p + n, hkv, d, seed=2)
+    out, lse = torch.zeros(n, hq, d, device=DEV, dtype=torch.bfloat16), torch.zeros(hq, n, device=DEV)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        attn.run(q, k, v, out, lse)
+    for i in range(4):
+        q.copy_(_rand(n, hq, d, seed=10 + i))
+        v.copy_(_rand(p + n, hkv, d, seed=20 + i))
+        ref, ref_lse = attn.run(q, k, v, torch.empty_like(out), torch.empty_like(lse))
+        torch.cuda.synchronize()
+        out.zero_()
+        lse.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref) and torch.equal(lse, ref_lse), "replay %d" % i
