@@ -1804,9 +1804,14 @@ Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPla
     const int fixed = c.num_splits >= 1 ? fixed_splits(c, max_prefix) : 0;
     Candidate best, x;
     std::vector<double> lanes;
-    // Candidates compare by their modelled time and what it leaves out: a pair's tiles
-    // share their key reads with the other slots of the segment, 4 to 8 % of a long
-    // launch, and a split must be worth its partials' memory.
+    // Candidates compare by their modelled time and what it leaves out: a split must be
+    // worth its partials' memory; pairs of one-head tiles share their key reads with the
+    // other slots of the segment, 2 to 9 % of a long launch (mla 6540 against 6703 us).
+    // Tiles of several heads are few tokens apart, so single ones, which all start at key
+    // 0, share them as well: up to 3 % faster than pairs (8192 rows of 64/4 heads without a
+    // prefix 1014 against 1048 us, 4096 of 32/8 behind 20480 1248 against 1262). In short
+    // launches of equal modelled time pairs start fewer workgroups (4096 rows of 32/8
+    // heads without a prefix 132.5 against 135.5 us).
     double best_score = 0.0;
     auto consider = [&](bool paired, bool split) {
         if (!fixed && !best.segs.empty() && partial_bytes(c, x.part_rows()) > max_part) return;
@@ -1815,7 +1820,8 @@ Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPla
         std::stable_sort(x.segs.begin(), x.segs.end(),
                          [](const SegPlan& a, const SegPlan& b) { return a.longest > b.longest; });
         x.t = model.launch(x.segs, x.nb, x.tt, lanes) + model.merge(x.part_rows());
-        const double score = x.t * (1.0 + (split ? 0.02 : 0.0) + (!paired && x.t > 400.0 ? 0.04 : 0.0));
+        const double order = pack > 1 ? (paired && x.t > 400.0 ? 0.01 : 0.0) : (!paired && x.t > 400.0 ? 0.04 : 0.0);
+        const double score = x.t * (1.0 + (split ? 0.02 : 0.0) + order);
         if (best.segs.empty() || score < best_score) {
             best = x;
             best_score = score;
@@ -2066,11 +2072,11 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
     p->table_bytes = p->groups.size() > INLINE_GROUPS || p->merges.size() > INLINE_GROUPS
                          ? p->groups.size() * sizeof(LaunchGroup) + p->merges.size() * sizeof(CombineSeg)
                          : 0;
-    // the workspace: the table (room for 32 bytes per work item), then the partials
-    const size_t head = align256(std::max<size_t>({p->table_bytes, (size_t)p->num_items * sizeof(WorkItem), 1}));
-    p->part_o_off = head;
-    p->part_lse_off = head + align256((size_t)part_rows * c.num_q_heads * c.head_dim_v * sizeof(float));
-    p->ws_bytes = p->part_lse_off + align256((size_t)part_rows * c.num_q_heads * sizeof(float));
+    // the workspace: the table, then the partials (at least 32 bytes per work item in all)
+    p->part_o_off = align256(std::max<size_t>(p->table_bytes, 1));
+    p->part_lse_off = p->part_o_off + align256((size_t)part_rows * c.num_q_heads * c.head_dim_v * sizeof(float));
+    p->ws_bytes = std::max(p->part_lse_off + align256((size_t)part_rows * c.num_q_heads * sizeof(float)),
+                           align256((size_t)p->num_items * sizeof(WorkItem)));
     *workspace_bytes = p->ws_bytes;
     return VPP_OK;
 }
