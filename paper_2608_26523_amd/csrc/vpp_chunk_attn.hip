@@ -1362,6 +1362,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, CombineTabl
             const int64_t off = (int64_t)(b < n ? b : b0) * pairs;
             l[j] = b < n ? pl[off] : -INFINITY;
             v[j] = *(const float4*)(po + off * DV);
+            if (b >= n) v[j] = {0.f, 0.f, 0.f, 0.f};  // a weight of 0 would make NaN of an infinite partial
         }
         const float m = fmaxf(mx, fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])));
         const float keep = mx == -INFINITY ? 0.f : __expf(mx - m);

@@ -132,3 +132,30 @@ def test_single_tokens(heads, dims):
     out_p, _ = attn.run_paged(q, kp, vp, table.to(DEV))
     torch.cuda.synchronize()
     assert torch.equal(out_p, out)
+
+
+@pytest.mark.parametrize("pieces", [2, 3, 5, 7, 9, 11, 16])
+def test_merge_keeps_infinities(pieces):
+    """An infinite V in the first piece (a key every row sees) gives that column's infinity, as
+    it does without a split, and leaves every other column as it is: the merge reads nothing past
+    a row's last piece, whatever the lane group's four places in flight hold."""
+    from paper_2608_26523_amd.attention import ChunkAttention
+    hq, hkv, d, n, p = 4, 2, 64, 5, 64 * 17
+    print("case:", pieces, flush=True)
+    q, k, v = _rand((n, hq, d), 1), _rand((n + p, hkv, d), 2), _rand((n + p, hkv, d), 3)
+    got = []
+    for splits in (1, pieces):
+        attn = ChunkAttention(hq, hkv, d, d, max_chunk_tokens=n, max_kv_len=n + p, num_splits=splits)
+        assert attn.plan([0, n], [0], [p]).num_splits == splits
+        res = []
+        for inf in (False, True):
+            x = v.clone()
+            if inf:
+                x[3, :, 7], x[3, :, 40] = float("inf"), -float("inf")
+            out, _ = attn.run(q, k, x, torch.empty((n, hq, d), dtype=torch.bfloat16, device=DEV))
+            torch.cuda.synchronize()
+            res.append(out.float())
+        got.append(res)
+    for plain, inf in got:
+        plain[..., 7], plain[..., 40] = float("inf"), -float("inf")
+        assert torch.equal(plain, inf)
