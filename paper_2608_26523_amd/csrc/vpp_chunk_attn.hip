@@ -1539,7 +1539,9 @@ struct SegPlan {
     int32_t seg, row0, len, prefix, kv_start;
     int32_t tiles, pieces;
     bool paired;
-    int64_t longest;  // keys of the longest slot (of the last piece)
+    int64_t whole;    // keys of the longest slot, unsplit
+    int64_t longest;  // and of the last piece, the longest
+    double key_steps; // 64-key steps of all tiles of a head group
     int32_t slots() const { return paired ? (tiles + 1) / 2 : tiles; }
 };
 
@@ -1671,22 +1673,30 @@ int64_t longest_slot(const SegPlan& s, int tt, int32_t begin, int32_t end) {
 // finishes first. Its constants are measured on one MI355X with normal operands.
 struct LaunchModel {
     int heads, pack, dqk, dv;
+    static constexpr int NUM_CU = 256, NXCD = 8;
 
     // One 64-key step of a workgroup takes `few` us while few of them run and `full` us
     // with every place taken: one 256-row workgroup a CU, or two of 128 rows. In
     // between the chip is held by power, which grows with the cube of its clock: 192 of
     // 256 places busy step 1.1 times as fast as all of them, not 1.33 times.
-    struct Speed { double few, full; };
-    Speed speed(int nb) const {
-        static const Speed table[2][3] = {{{0.64, 1.22}, {0.84, 1.85}, {1.08, 2.15}},
-                                          {{1.03, 1.20}, {1.31, 1.72}, {1.52, 2.04}}};
+    struct Speed {
+        double few, full;
+        double step[2 * NUM_CU / NXCD];  // with (i + 1) * NXCD workgroups in flight
+        double rate = 0.0;               // the most steps per us of any of those
+        Speed(int nb, double few, double full) : few(few), full(full) {
+            for (int i = 0; i < NUM_CU / NXCD * (3 - nb); ++i) {
+                const double wgs = (i + 1) * NXCD;
+                if (nb == 2) step[i] = std::max(few, full * cbrt(wgs / NUM_CU));
+                else if (wgs <= NUM_CU) step[i] = std::max(few, 1.17 * few * cbrt(wgs / NUM_CU));
+                else step[i] = full * cbrt(wgs / (2 * NUM_CU));  // while any CU holds two, those set the pace
+                rate = std::max(rate, wgs / step[i]);
+            }
+        }
+    };
+    const Speed& speed(int nb) const {
+        static const Speed table[2][3] = {{{1, 0.64, 1.22}, {1, 0.84, 1.85}, {1, 1.08, 2.15}},
+                                          {{2, 1.03, 1.20}, {2, 1.31, 1.72}, {2, 1.52, 2.04}}};
         return table[nb - 1][dqk == 64 ? 0 : dqk == 128 ? 1 : 2];
-    }
-    // a step with `wgs` workgroups in flight
-    static double step(const Speed& v, int nb, double wgs) {
-        if (nb == 2) return std::max(v.few, v.full * cbrt(wgs / NUM_CU));
-        if (wgs <= NUM_CU) return std::max(v.few, 1.17 * v.few * cbrt(wgs / NUM_CU));
-        return v.full * cbrt(wgs / (2 * NUM_CU));  // while any CU holds two, those set the pace
     }
     // What a tile costs beside its steps, in steps: Q load, pipeline fill, first and
     // last step, store. Two 128-row workgroups a CU hide much of each other's.
@@ -1694,7 +1704,6 @@ struct LaunchModel {
     // The rate at which workgroups stream distinct keys, one or two in flight per CU:
     // it holds back the steps of segments with few tiles.
     double stream(int nb) const { return nb == 1 ? 6.0e6 : 3.8e6; }  // bytes per us
-    static constexpr int NUM_CU = 256, NXCD = 8;
 
     // Time of the merge of part_rows partial rows: a launch, and the partials written
     // and read back.
@@ -1702,73 +1711,115 @@ struct LaunchModel {
         return part_rows == 0 ? 0.0 : 4.0 + 2.0 * (double)part_rows * heads * (4.0 * dv + 4.0) / 5.0e6;
     }
 
+    // Steps of all tiles and pieces of a segment, one head group: fixed costs included.
+    double steps(const SegPlan& s, int nb) const {
+        return s.key_steps + (double)s.tiles * s.pieces * tile(nb);
+    }
+    // Bytes of distinct keys and values a launch reads.
+    double key_bytes(const std::vector<SegPlan>& segs) const {
+        double rows = 0.0;
+        for (const SegPlan& s : segs) rows += (double)s.prefix + s.len;
+        return rows * (heads / pack) * (dqk + dv) * 2.0;
+    }
+    // The time no launch of `all` steps of its workgroups comes under: the most steps per us
+    // that any number of workgroups makes, and the rate of its keys.
+    double bound(double all, double bytes, int nb) const {
+        return std::max(all / speed(nb).rate, bytes / stream(nb));
+    }
+
     // Time of a launch of `segs` (longest slots first): one XCD's share of each group
     // (work_coords), placed in order on whichever of its workgroup places frees first.
     // All places progress alike, so the schedule is found in steps and then put on the
     // clock.
-    double launch(const std::vector<SegPlan>& segs, int nb, int tt, std::vector<double>& lanes) const {
+    double launch(const std::vector<SegPlan>& segs, int nb, int tt, std::vector<double>& lanes,
+                  std::vector<double>& costs) const {
         const int64_t groups = heads / pack;
         const int places = NUM_CU / NXCD * (3 - nb);
         const double c_tile = tile(nb);
-        double bytes = 0.0;
         lanes.assign((size_t)places, 0.0);
+        double left = 0.0;  // steps of one place still to come, if spread evenly
+        for (const SegPlan& s : segs) left += steps(s, nb) * groups / (NXCD * places);
+        double even = 0.0;               // steps every place has had alike
+        double placed = 0.0, top = 0.0;  // beside those: the mean and the most of a place
         int64_t seen = 0;
         for (const SegPlan& s : segs) {
-            bytes += (double)groups * ((double)s.prefix + s.len) * (dqk + dv) * 2.0;
             const int64_t n = s.slots() * groups * s.pieces;
             int64_t share = (seen + n + NXCD - 1) / NXCD - (seen + NXCD - 1) / NXCD;
             seen += n;
-            int32_t kb = 0, ke = INT32_MAX;
-            auto cost = [&](int i) {
+            // While twice a segment's longest slot and what the fullest place is ahead are
+            // still to come on every place, the shorter slots behind even out whatever the
+            // segment's own placing would leave uneven.
+            const double own = steps(s, nb) * groups / (NXCD * places);
+            left -= own;
+            const bool evens_out = top - placed <= left;
+            if (evens_out && 2.0 * ((double)s.longest / BN + 2.0 * c_tile) < left) {
+                even += own;
+                continue;
+            }
+            placed += own;
+            // every `stride`-th slot of its heads, longest first where slots are single tiles
+            const int64_t h = groups * s.pieces;
+            const int stride = s.paired ? 1 : (int)(NXCD / std::min<int64_t>(NXCD, h & -h));
+            const int64_t all = share;
+            // many rounds of one segment fill the places evenly: only a few are placed,
+            // taken evenly from its slots
+            if (share > (evens_out ? 5 : 8) * places) {
+                share = share % places + 4 * places;
+                const double spread = own * (double)(all - share) / (double)all;
+                even += spread;
+                placed -= spread;
+            }
+            if (share == 0) continue;
+            // slot i of a head group, piece by piece from the last on, in launch order
+            const int64_t ring = (int64_t)s.slots() * s.pieces;
+            auto cost = [&](int64_t i) {
+                const int b = (int)(i / s.slots()), at = (int)(i - (int64_t)b * s.slots()), piece = s.pieces - 1 - b;
+                const int32_t kb = s.pieces == 1 ? 0 : piece_begin(s.prefix, s.pieces, piece);
+                const int32_t ke = b == 0 ? INT32_MAX : piece_begin(s.prefix, s.pieces, piece + 1);
                 double t = 0.0;
                 for (int which = 0; which < 2; ++which) {
-                    const int tl = slot_tile(s, i, which);
+                    const int tl = slot_tile(s, s.paired ? at : s.slots() - 1 - at, which);
                     if (tl >= 0) t += (double)((tile_keys(s, tt, tl, kb, ke) + BN - 1) / BN) + c_tile;
                 }
                 return t;
             };
-            // every `stride`-th slot of its heads, longest first where slots are single tiles
-            const int64_t h = groups * s.pieces;
-            const int stride = s.paired ? 1 : (int)(NXCD / std::min<int64_t>(NXCD, h & -h));
-            int skip = 0;
-            // many rounds of one segment fill the places evenly: only the last few are
-            // placed, taken evenly from its slots
-            if (share > 8 * places) {
-                double sum = 0.0;
-                const int period = std::min(s.slots(), 16);
-                for (int i = 0; i < period; ++i) sum += cost((int)((int64_t)i * s.slots() / period));
-                sum /= (double)period * s.pieces;  // the pieces of a slot together cost about the whole
-                const int64_t whole = share / places - 4;
-                for (double& t : lanes) t += sum * (double)whole;
-                skip = (int)(share / (share - whole * places)) - 1;
-                share -= whole * places;
+            const bool again = ring < share;  // head groups repeat the same costs
+            if (again) {
+                costs.resize((size_t)ring);
+                for (int64_t i = 0; i < ring; ++i) costs[(size_t)i] = cost(i);
             }
-            int piece = s.pieces - 1, slot = 0;
-            auto bounds = [&]() {
-                if (s.pieces == 1) return;
-                kb = piece_begin(s.prefix, s.pieces, piece);
-                ke = piece + 1 == s.pieces ? INT32_MAX : piece_begin(s.prefix, s.pieces, piece + 1);
-            };
-            bounds();
+            const int64_t step = stride * (all / share), rest = all % share;
+            int64_t i = 0, err = 0;
             for (int64_t j = 0; j < share; ++j) {
-                std::pop_heap(lanes.begin(), lanes.end(), std::greater<double>());
-                lanes.back() += cost(s.paired ? slot : s.slots() - 1 - slot);
-                std::push_heap(lanes.begin(), lanes.end(), std::greater<double>());
-                for (slot += stride * (1 + skip); slot >= s.slots(); slot -= s.slots()) {
-                    piece = piece == 0 ? s.pieces - 1 : piece - 1;
-                    bounds();
+                // the place that frees first is the heap's root: give it the slot, sift it down
+                const double t = lanes[0] + (again ? costs[(size_t)i] : cost(i));
+                int at = 0;
+                for (int c = 1; c < places; c = 2 * at + 1) {
+                    if (c + 1 < places) c += lanes[(size_t)c + 1] < lanes[(size_t)c];
+                    if (lanes[(size_t)c] >= t) break;
+                    lanes[(size_t)at] = lanes[(size_t)c];
+                    at = c;
                 }
+                lanes[(size_t)at] = t;
+                top = std::max(top, t);
+                i += step;
+                if ((err += rest) >= share) {
+                    err -= share;
+                    i += stride;
+                }
+                if (i >= ring) i = i < 2 * ring ? i - ring : i % ring;
             }
         }
         double steps = 0.0;
-        for (double l : lanes) steps += l * NXCD;
+        for (double& l : lanes) steps += (l += even) * NXCD;
         std::sort(lanes.begin(), lanes.end());
-        const Speed v = speed(nb);
-        const double stream_step = bytes / steps / stream(nb);  // us a step of each workgroup
+        const Speed& v = speed(nb);
+        const double stream_step = key_bytes(segs) / steps / stream(nb);  // us a step of each workgroup
         double t = 0.0, at = 0.0;
         for (int i = 0; i < places; ++i) {
+            if (lanes[(size_t)i] == at) continue;
             const double wgs = (double)(places - i) * NXCD;
-            t += (lanes[(size_t)i] - at) * std::max(step(v, nb, wgs), wgs * stream_step);
+            t += (lanes[(size_t)i] - at) * std::max(v.step[places - 1 - i], wgs * stream_step);
             at = lanes[(size_t)i];
         }
         return t;
@@ -1804,7 +1855,8 @@ Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPla
     for (const SegPlan& s : segs) max_prefix = std::max<int64_t>(max_prefix, s.prefix);
     const int fixed = c.num_splits >= 1 ? fixed_splits(c, max_prefix) : 0;
     Candidate best, x;
-    std::vector<double> lanes;
+    std::vector<double> lanes, costs;
+    const double bytes = model.key_bytes(segs);
     // Candidates compare by their modelled time and what it leaves out: a split must be
     // worth its partials' memory; pairs of one-head tiles share their key reads with the
     // other slots of the segment, 2 to 9 % of a long launch (mla 6540 against 6703 us).
@@ -1814,37 +1866,58 @@ Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPla
     // launches of equal modelled time pairs start fewer workgroups (4096 rows of 32/8
     // heads without a prefix 132.5 against 135.5 us).
     double best_score = 0.0;
+    // Whether the candidate was weighed: false if even its work spread evenly would take
+    // longer than the best one does (more pieces only add to that). Most go this way: a
+    // launch is placed for 2 to 8 of up to 36 candidates.
     auto consider = [&](bool paired, bool split) {
-        if (!fixed && !best.segs.empty() && partial_bytes(c, x.part_rows()) > max_part) return;
+        const int64_t part_rows = x.part_rows();
+        if (!fixed && !best.segs.empty() && partial_bytes(c, part_rows) > max_part) return true;
+        const double handicap = split ? 1.02 : 1.0, merge = model.merge(part_rows);
+        if (!best.segs.empty()) {
+            double all = 0.0;
+            for (const SegPlan& s : x.segs) all += model.steps(s, x.nb) * groups;
+            if ((model.bound(all, bytes, x.nb) + merge) * handicap >= best_score) return false;
+        }
         for (SegPlan& s : x.segs)
-            s.longest = longest_slot(s, x.tt, s.pieces > 1 ? piece_begin(s.prefix, s.pieces, s.pieces - 1) : 0, INT32_MAX);
+            s.longest = s.pieces == 1 ? s.whole : longest_slot(s, x.tt, piece_begin(s.prefix, s.pieces, s.pieces - 1), INT32_MAX);
         std::stable_sort(x.segs.begin(), x.segs.end(),
                          [](const SegPlan& a, const SegPlan& b) { return a.longest > b.longest; });
-        x.t = model.launch(x.segs, x.nb, x.tt, lanes) + model.merge(x.part_rows());
+        x.t = model.launch(x.segs, x.nb, x.tt, lanes, costs) + merge;
         const double order = pack > 1 ? (paired && x.t > 400.0 ? 0.01 : 0.0) : (!paired && x.t > 400.0 ? 0.04 : 0.0);
-        const double score = x.t * (1.0 + (split ? 0.02 : 0.0) + order);
+        const double score = x.t * (handicap + order);
         if (best.segs.empty() || score < best_score) {
             best = x;
             best_score = score;
         }
+        return true;
     };
-    for (int nb : {2, 1}) {
+    // first the variant whose launch would be the shorter one if spread evenly
+    auto evenly = [&](int nb) {
+        double all = 0.0;
+        for (const SegPlan& s : segs)
+            all += (double)groups * ceil((double)s.len * pack / block_rows(nb)) * (s.prefix + 0.5 * s.len) / BN;
+        return model.bound(all, bytes, nb);
+    };
+    const int first = nb_mask == 3 && evenly(1) < evenly(2) ? 1 : 2;
+    for (int nb : {first, 3 - first}) {
         if (!(nb_mask & nb)) continue;
         x.nb = nb;
         x.tt = block_rows(nb) / pack;
         // the launch's work if spread evenly: steps of one workgroup place, and its time
-        double steps = 0.0, bytes = 0.0;
-        for (const SegPlan& s : segs) {
-            steps += (double)groups * ((s.len + x.tt - 1) / x.tt) * (((double)s.prefix + 0.5 * s.len) / BN + 1.0);
-            bytes += (double)groups * ((double)s.prefix + s.len) * (c.head_dim_qk + c.head_dim_v) * 2.0;
+        double steps = 0.0;
+        std::vector<SegPlan> base = segs;
+        for (SegPlan& s : base) {
+            s.tiles = (int32_t)(((int64_t)s.len + x.tt - 1) / x.tt);
+            for (int t = 0; t < s.tiles; ++t) s.key_steps += (double)((tile_keys(s, x.tt, t, 0, INT32_MAX) + BN - 1) / BN);
+            steps += (double)groups * s.tiles * (((double)s.prefix + 0.5 * s.len) / BN + 1.0);
         }
         const double even = steps / (LaunchModel::NUM_CU * (3 - nb));
         const double bound = std::max(even * model.speed(nb).full, bytes / model.stream(nb));
         for (int paired = 1; paired >= 0; --paired) {
-            x.segs = segs;
+            x.segs = base;
             for (SegPlan& s : x.segs) {
-                s.tiles = (int32_t)(((int64_t)s.len + x.tt - 1) / x.tt);
                 s.paired = paired != 0;
+                s.whole = longest_slot(s, x.tt, 0, INT32_MAX);
                 s.pieces = fixed > 1 ? (int)std::min<int64_t>(fixed, std::max(1, s.prefix / BN)) : 1;
             }
             consider(paired != 0, false);
@@ -1852,16 +1925,14 @@ Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPla
             double last_t = 1e30;
             for (double f : {2.0, 1.0, 0.7, 0.5, 0.35, 0.25, 0.17, 0.12}) {
                 const double target = std::max(even * f, 4.0);  // steps of a workgroup
-                bool split = false;
+                bool changed = false;
                 for (SegPlan& s : x.segs) {
-                    s.pieces = 1;
-                    const double longest = (double)longest_slot(s, x.tt, 0, INT32_MAX) / BN;
-                    const int64_t cap = std::min<int64_t>(MAX_PIECES, s.prefix / MIN_PIECE);
-                    s.pieces = (int)std::max<int64_t>(1, std::min<int64_t>(cap, (int64_t)ceil(longest / target)));
-                    split = split || s.pieces > 1;
+                    const int32_t before = s.pieces, cap = std::min<int32_t>(MAX_PIECES, s.prefix / MIN_PIECE);
+                    s.pieces = std::max(1, (int)std::min<double>(cap, ceil((double)s.whole / BN / target)));
+                    changed = changed || s.pieces != before;
                 }
-                if (!split) continue;
-                consider(paired != 0, true);
+                if (!changed) continue;
+                if (!consider(paired != 0, true)) break;
                 if (target <= 4.0 || (x.t > last_t && x.t > 1.1 * best.t) || best.t < 1.04 * bound) break;
                 last_t = x.t;
             }
@@ -2001,7 +2072,7 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
         for (int s = 0; s < num_segments; ++s) {
             const int32_t len = cu_q[s + 1] - cu_q[s];
             if (len == 0) continue;
-            segs.push_back({s, cu_q[s], len, (int32_t)prefix_len[s], (int32_t)kv_start[s], 0, 1, true, 0});
+            segs.push_back({s, cu_q[s], len, (int32_t)prefix_len[s], (int32_t)kv_start[s], 0, 1, true, 0, 0, 0.0});
             // visible pairs: sum over rows of (position + 1)
             pairs += (double)len * (double)prefix_len[s] + 0.5 * (double)len * (len + 1.0);
             max_rows = std::max<int64_t>(max_rows, (int64_t)len * pack);
