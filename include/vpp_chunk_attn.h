@@ -100,7 +100,12 @@ typedef struct vpp_chunk_attn_plan_s* vpp_chunk_attn_plan_t;
  * slot of its own (a ring of 4 per plan); only a run that reuses a slot whose
  * earlier copy is still in flight waits, on the host, for that copy.
  * *workspace_bytes receives the bytes of device workspace vpp_chunk_attn_run
- * needs for this plan (always > 0). The arrays are not retained.
+ * needs for this plan (always > 0): the launch table past 64 segments, and, for
+ * each segment whose key range is split, pieces * rows * Hq * (dv + 1) fp32
+ * partials (at least 32 bytes per work item of vpp_chunk_attn_plan_items, up to
+ * 1 MiB). Automatic plans (num_splits = -1) split where that is modelled to be
+ * faster, so chunks of one size may need 256 bytes or a hundred MB: size the
+ * workspace from this value, chunk by chunk. The arrays are not retained.
  */
 vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg,
                                  int32_t num_segments, const int32_t* cu_q,

@@ -1943,7 +1943,7 @@ Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPla
 
 // The split count of one-head tiles run in pairs, from a launch placed head by head:
 // the rule by which a plan's workspace fits vpp_chunk_attn_run_noalloc's scratch or not.
-// A chunk whose workspace it keeps within the scratch stays within it (split_limit).
+// A chunk whose workspace it keeps within the scratch stays within it.
 int one_head_splits(const vpp_chunk_attn_config_t& c, std::vector<SegPlan> segs, int nb, int64_t max_prefix,
                     int32_t tokens) {
     constexpr int NXCD = LaunchModel::NXCD;
@@ -2084,7 +2084,8 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
             plan = choose_plan(c, segs, nb_mask, pack, SIZE_MAX);
             // a chunk that one-head tiles in pairs would keep within the scratch of
             // run_noalloc stays within it
-            const size_t room = VPP_NOALLOC_SCRATCH_BYTES - (4u << 20);
+            const size_t table = std::max<size_t>(4u << 20, align256(segs.size() * (sizeof(LaunchGroup) + sizeof(CombineSeg))));
+            const size_t room = (size_t)VPP_NOALLOC_SCRATCH_BYTES - std::min<size_t>(table, VPP_NOALLOC_SCRATCH_BYTES);
             if (c.num_splits < 1 && partial_bytes(c, plan.part_rows()) > room) {
                 const int one_head_nb = forced_nb() ? forced_nb() : small ? 1 : 2;
                 const int n = one_head_splits(c, segs, one_head_nb, max_prefix, cu_q[num_segments]);
@@ -2144,11 +2145,13 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
     p->table_bytes = p->groups.size() > INLINE_GROUPS || p->merges.size() > INLINE_GROUPS
                          ? p->groups.size() * sizeof(LaunchGroup) + p->merges.size() * sizeof(CombineSeg)
                          : 0;
-    // the workspace: the table, then the partials (at least 32 bytes per work item in all)
+    // The workspace: the table, then the partials. Callers that size it from plan_items find 32
+    // bytes for each of those up to 1 MiB; the listing itself grows with the most pieces of any
+    // segment times all slots, far past what a launch of many segments uses.
     p->part_o_off = align256(std::max<size_t>(p->table_bytes, 1));
     p->part_lse_off = p->part_o_off + align256((size_t)part_rows * c.num_q_heads * c.head_dim_v * sizeof(float));
     p->ws_bytes = std::max(p->part_lse_off + align256((size_t)part_rows * c.num_q_heads * sizeof(float)),
-                           align256((size_t)p->num_items * sizeof(WorkItem)));
+                           std::min<size_t>(align256((size_t)p->num_items * sizeof(WorkItem)), 1u << 20));
     *workspace_bytes = p->ws_bytes;
     return VPP_OK;
 }
