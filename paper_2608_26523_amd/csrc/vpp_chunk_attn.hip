@@ -1406,7 +1406,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, CombineTabl
         mx = m;
     }
     if (!valid) return;
-    const float inv = 1.f / den;
+    const float inv = den > 0.f ? 1.f / den : 0.f;  // no visible key has any weight: zeros, as without a split
     bf16x4 r;
 #pragma unroll
     for (int j = 0; j < 4; ++j) r[j] = (__bf16)(acc[j] * inv);

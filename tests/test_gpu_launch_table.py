@@ -159,3 +159,27 @@ def test_merge_keeps_infinities(pieces):
     for plain, inf in got:
         plain[..., 7], plain[..., 40] = float("inf"), -float("inf")
         assert torch.equal(plain, inf)
+
+
+@pytest.mark.parametrize("pieces", [2, 5, 16])
+def test_merge_of_rows_without_weight(pieces):
+    """Rows whose every score is -inf give zeros and lse -inf, split as unsplit: no piece of
+    such a row has any weight."""
+    from paper_2608_26523_amd.attention import ChunkAttention
+    hq, hkv, d, n, p = 4, 2, 64, 5, 64 * 17
+    print("case:", pieces, flush=True)
+    q, k, v = _rand((n, hq, d), 1), _rand((n + p, hkv, d), 2), _rand((n + p, hkv, d), 3)
+    q[:, 1], k[:, 0] = 1.0, -float("inf")  # head 1 (kv head 0)
+    q[:, 0] = 0.5                          # head 0 reads the same keys
+    got = []
+    for splits in (1, pieces):
+        attn = ChunkAttention(hq, hkv, d, d, max_chunk_tokens=n, max_kv_len=n + p, num_splits=splits)
+        assert attn.plan([0, n], [0], [p]).num_splits == splits
+        out = torch.empty((n, hq, d), dtype=torch.bfloat16, device=DEV)
+        lse = torch.empty((hq, n), dtype=torch.float32, device=DEV)
+        attn.run(q, k, v, out, lse)
+        torch.cuda.synchronize()
+        got.append((out, lse))
+    for out, lse in got:
+        assert (out[:, :2] == 0).all() and (lse[:2] == -float("inf")).all()
+        assert torch.isfinite(out[:, 2:].float()).all() and torch.isfinite(lse[2:]).all()
