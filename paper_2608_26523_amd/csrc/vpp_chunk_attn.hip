@@ -40,8 +40,8 @@
 #include "vpp_chunk_attn.h"
 
 // VPP_PART: 0 = host code and the contiguous-cache kernels, 1 = the paged-cache
-// kernels, 2 = the split-key-layout kernels; unset (3) = everything in one
-// translation unit.
+// kernels, 2 = the split-key-layout kernels, 4 = the host code alone (for a test that
+// replays launches on the CPU); unset (3) = everything in one translation unit.
 #ifndef VPP_PART
 #define VPP_PART 3
 #endif
@@ -326,23 +326,34 @@ __device__ __forceinline__ T* const_ptr(uint64_t p) {
     return (T*)(uintptr_t)p;
 }
 
-// Index of the last of `n` table entries (bytes `stride` apart, their first word
-// ascending and the first entry's <= x) whose first word is <= x. Each step
-// compares 64 of them at once, one per lane: one step up to 64 entries, two up to
-// 4096.
+// What a workgroup works on -- its table entry, tiles, keys and where the results go --
+// is worked out by the functions from here to merge_place, on the host as well: a CPU
+// test replays every workgroup of a launch through them.
+
+// Search for the last of n table entries (their first word ascending, the first
+// entry's <= x) whose first word is <= x: entries [lo, lo + cnt) are left. Each step
+// compares 64 of them at once, one per lane: one step up to 64 entries, two up to 4096.
+struct EntrySearch {
+    int lo, cnt;
+    __host__ __device__ int step() const { return (cnt + 63) >> 6; }
+    __host__ __device__ bool has(int lane) const { return lane * step() < cnt; }
+    __host__ __device__ int entry(int lane) const { return lo + min(lane * step(), cnt - 1); }  // a lane's entry
+    __host__ __device__ void take(int hits) {  // how many lanes have an entry that is <= x
+        const int s = step(), skip = (hits - 1) * s;
+        lo += skip;
+        cnt = min(s, cnt - skip);
+    }
+};
+// The entry of x in a table of entries `stride` bytes apart.
 __device__ __forceinline__ int find_entry(uint64_t table, int stride, int n, int x) {
     const int lane = threadIdx.x & 63;
-    int lo = 0, cnt = n;
-    while (cnt > 1) {
-        const int step = (cnt + 63) >> 6;
-        const int off = lane * step;
-        const int idx = lo + min(off, cnt - 1);
-        const int first = *(__attribute__((address_space(1))) const int32_t*)(uintptr_t)(table + (uint64_t)idx * stride);
-        const int p = __popcll(__builtin_amdgcn_ballot_w64(off < cnt && first <= x)) - 1;
-        lo += p * step;
-        cnt = min(step, cnt - p * step);
+    EntrySearch e{0, n};
+    while (e.cnt > 1) {
+        const int first =
+            *(__attribute__((address_space(1))) const int32_t*)(uintptr_t)(table + (uint64_t)e.entry(lane) * stride);
+        e.take(__popcll(__builtin_amdgcn_ballot_w64(e.has(lane) && first <= x)));
     }
-    return __builtin_amdgcn_readfirstlane(lo);
+    return __builtin_amdgcn_readfirstlane(e.lo);
 }
 
 // Workgroup i of a group -> (slot, head), `heads` counting split pieces too (the
@@ -353,7 +364,7 @@ __device__ __forceinline__ int find_entry(uint64_t table, int stride, int n, int
 // share a head take turns at its slots, longest first (contiguous runs gave one XCD
 // the short half and the next the long half of a causal segment: 1120 us where pairs
 // take 984, at 6915 rows and 64/4 heads). Every group is spread over all XCDs.
-__device__ __forceinline__ void work_coords(int i, int slots, int heads, bool paired, bool remap, int& slot, int& head) {
+__host__ __device__ __forceinline__ void work_coords(int i, int slots, int heads, bool paired, bool remap, int& slot, int& head) {
     if (remap && paired) {
         const int n = slots * heads;
         const int x = i & 7;
@@ -365,6 +376,44 @@ __device__ __forceinline__ void work_coords(int i, int slots, int heads, bool pa
     head = slots == 1 ? i : i / slots;
     slot = i - head * slots;
     if (!paired) slot = slots - 1 - slot;
+}
+
+// Token of a tile's row r, r < 256 (AttnArgs::pack_magic).
+__host__ __device__ __forceinline__ int row_token(int r, int magic) { return (int)((uint32_t)r * (uint32_t)magic >> 16); }
+
+// A workgroup's first (sub = 0) or second tile.
+struct TileWork {
+    int h, hk;                    // first query head, kv head
+    int row0, nrows, pos0;        // first chunk row, rows (tokens), in-request position of the first
+    int key_begin, key_end;       // keys of the request that this piece covers
+    int out_row0;                 // where the results go: row0, or ~ the first partial row
+};
+// false: the workgroup has no such tile. `block` counts from the group's first workgroup.
+template <typename Args, typename Group>
+__host__ __device__ __forceinline__ bool tile_work(const Args& a, const Group& g, int block, int sub, TileWork& w) {
+    const int slots = g.slots, seg_tiles = g.tiles, pieces = g.pieces;
+    const bool paired = slots != seg_tiles;
+    int slot, hg, piece = 0, piece_kb = 0, piece_ke = INT32_MAX;  // hg: head group
+    work_coords(block, slots, a.head_groups * pieces, paired, a.xcd_remap != 0, slot, hg);
+    if (pieces > 1) {
+        const int hp = hg;
+        hg = hp / pieces;
+        piece = pieces - 1 - (hp - hg * pieces);  // the last piece is the longest: first
+        piece_kb = piece_begin(g.prefix, pieces, piece);
+        if (piece + 1 < pieces) piece_ke = piece_begin(g.prefix, pieces, piece + 1);
+    }
+    const int ti = sub == 0 ? slot : seg_tiles - 1 - slot;
+    if (sub == 1 && (!paired || ti == slot)) return false;
+    const int t_row0 = ti * a.tile_tokens;  // the tile's first token in the segment
+    w.h = hg * a.pack;
+    w.hk = a.pack == a.group ? hg : w.h / a.group;
+    w.row0 = g.row0 + t_row0;
+    w.nrows = min(a.tile_tokens, g.len - t_row0);
+    w.pos0 = g.prefix + t_row0;
+    w.key_begin = piece_kb;
+    w.key_end = min(piece_ke, w.pos0 + w.nrows);
+    w.out_row0 = g.part0 < 0 ? w.row0 : ~(g.part0 + piece * g.len + t_row0);
+    return true;
 }
 
 template <int DQK, int DV, int NB>
@@ -730,7 +779,6 @@ void attn_fwd_kernel(AttnArgs args, GroupTable) {
                      : (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(AttnArgs);
     };
     const int gidx0 = find_entry(group_base(args.groups), sizeof(LaunchGroup), args.num_groups, (int)blockIdx.x);
-    auto row_token = [](int r, int magic) { return (int)((uint32_t)r * (uint32_t)magic >> 16); };
     // A slot holds up to two tiles of the segment: the first runs its key range
     // ascending, its partner from the other end (if any) descending.
 #pragma nounroll
@@ -743,34 +791,13 @@ void attn_fwd_kernel(AttnArgs args, GroupTable) {
         asm volatile("" : "+s"(gidx), "+s"(ap));
         const_args_t& a = *ap;
         const_group_t* const grp = const_ptr<const_group_t>(group_base(a.groups)) + gidx;
-        const int slots = grp->slots, seg_tiles = grp->tiles, pieces = grp->pieces;
-        const bool paired = slots != seg_tiles;
-        int slot, hg, piece = 0, piece_kb = 0, piece_ke = INT32_MAX;  // hg: head group
-        work_coords((int)blockIdx.x - grp->wg0, slots, a.head_groups * pieces, paired, a.xcd_remap != 0, slot, hg);
-        if (pieces > 1) {
-            const int hp = hg;
-            hg = hp / pieces;
-            piece = pieces - 1 - (hp - hg * pieces);  // the last piece is the longest: first
-            piece_kb = piece_begin(grp->prefix, pieces, piece);
-            if (piece + 1 < pieces) piece_ke = piece_begin(grp->prefix, pieces, piece + 1);
-        }
-        const int h = hg * a.pack;  // the tile's first head
-        const int ti = sub == 0 ? slot : seg_tiles - 1 - slot;
-        if (sub == 1 && (!paired || ti == slot)) break;
-        const int t_row0 = ti * a.tile_tokens;  // the tile's first token in the segment
-        struct { int row0, nrows, pos0, key_begin, key_end; } it;
-        it.row0 = grp->row0 + t_row0;
-        it.nrows = min(a.tile_tokens, grp->len - t_row0);
-        it.pos0 = grp->prefix + t_row0;
-        it.key_begin = piece_kb;
-        it.key_end = min(piece_ke, it.pos0 + it.nrows);
+        TileWork it;
+        if (!tile_work(a, *grp, (int)blockIdx.x - grp->wg0, sub, it)) break;
+        const int h = it.h, hk = it.hk, out_row0 = it.out_row0;
         const int64_t kv_start = grp->kv_start;
-        // where the results go: the tile's first chunk row, or ~ its first partial row
-        const int out_row0 = grp->part0 < 0 ? it.row0 : ~(grp->part0 + piece * grp->len + t_row0);
         // every wave is done with the LDS tiles of the slot's previous tile before
         // this tile's first copies overwrite them
         lds_barrier();
-        const int hk = a.pack == a.group ? hg : h / a.group;
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));  // nor any lane's offsets vector registers
         const int lane = tid & 63;
@@ -1329,6 +1356,14 @@ __host__ __device__ constexpr int merge_ways(int pieces) {
     return pieces >= 16 ? 8 : pieces >= 8 ? 4 : pieces >= 4 ? 2 : 1;
 }
 
+// (row, head) pair of a segment -- of its len * num_heads in that order -- that lane group
+// `grp` of `groups` merges in the segment's block `block`; `way`: the pieces it takes,
+// every ways-th from `way` on. Past the last pair: none.
+__host__ __device__ __forceinline__ int64_t merge_place(int block, int groups, int grp, int ways, int& way) {
+    way = grp % ways;
+    return (int64_t)block * (groups / ways) + grp / ways;
+}
+
 // Merge of split partials: lse = log sum_b exp(lse_b); out = sum_b exp(lse_b - lse) O_b.
 // DV/4 threads a lane group, 4 values each; a block stays within one segment.
 template <int DV>
@@ -1341,9 +1376,9 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, CombineTabl
     const int len = sg->len, n = sg->pieces;
     const int ways = merge_ways(n);
     const int grp = threadIdx.x / G, c = threadIdx.x % G;
-    const int way = grp % ways;
+    int way;
     const int64_t pairs = (int64_t)len * a.num_heads;
-    const int64_t pair = (int64_t)((int)blockIdx.x - sg->block0) * (GROUPS / ways) + grp / ways;
+    const int64_t pair = merge_place((int)blockIdx.x - sg->block0, GROUPS, grp, ways, way);
     const bool valid = pair < pairs;
     const int64_t at = valid ? pair : pairs - 1;  // spare groups repeat the last pair, and store nothing
     const int row = (int)(at / a.num_heads);
@@ -1466,7 +1501,7 @@ hipError_t vpp_detail::launch_attn_paged(const Launch& l, hipStream_t stream) { 
 hipError_t vpp_detail::launch_attn_rope(const Launch& l, hipStream_t stream) { return launch_dims<KV_ROPE>(l, stream); }
 #endif
 
-#if VPP_PART == 0 || VPP_PART == 3
+#if VPP_PART == 0 || VPP_PART == 3 || VPP_PART == 4
 
 // Scatter of a chunk's new K/V rows into a paged cache: the write that puts a
 // chunk's own keys and values in the cache before its attention (section 2.4).
@@ -2273,6 +2308,20 @@ struct RopeK {
     int64_t kr_st;
 };
 
+// The plan's part of the kernel arguments.
+void plan_args(const vpp_chunk_attn_plan_s* p, AttnArgs& a) {
+    const vpp_chunk_attn_config_t& c = p->cfg;
+    a.num_groups = (int32_t)p->groups.size();
+    a.num_heads = c.num_q_heads;
+    a.group = c.num_q_heads / c.num_kv_heads;
+    a.pack = p->pack;
+    a.pack_magic = (65536 + p->pack - 1) / p->pack;  // exact for r < 256, pack <= 16
+    a.tile_tokens = p->tile_tokens;
+    a.head_groups = c.num_q_heads / p->pack;
+    a.scale_log2 = (float)((double)p->scale * 1.4426950408889634);
+    a.xcd_remap = env_xcd_remap();
+}
+
 // How run_impl puts a launch table too large for the kernel arguments into the
 // workspace: through the plan's pinned staging ring (asynchronous), or straight
 // from the plan's host memory, which allocates nothing (the copy out of memory
@@ -2354,7 +2403,7 @@ vpp_status_t run_impl(vpp_chunk_attn_plan_t p, const void* q, int64_t q_st, int6
     l.nt = p->nt;
     l.workgroups = p->workgroups;
     AttnArgs& a = l.a;
-    a.num_groups = (int32_t)p->groups.size();
+    plan_args(p, a);
     if (p->table_bytes) a.groups = (const LaunchGroup*)ws;
     else memcpy(l.groups.g, p->groups.data(), groups_bytes);
     a.q = (const u16*)q;
@@ -2367,14 +2416,6 @@ vpp_status_t run_impl(vpp_chunk_attn_plan_t p, const void* q, int64_t q_st, int6
     a.q_st = (int32_t)q_st; a.q_sh = (int32_t)q_sh; a.k_st = (int32_t)k_st; a.k_sh = (int32_t)k_sh;
     a.v_st = (int32_t)v_st; a.v_sh = (int32_t)v_sh; a.o_st = (int32_t)o_st; a.o_sh = (int32_t)o_sh;
     a.lse_sh = (int32_t)lse_sh;
-    a.num_heads = c.num_q_heads;
-    a.group = c.num_q_heads / c.num_kv_heads;
-    a.pack = p->pack;
-    a.pack_magic = (65536 + p->pack - 1) / p->pack;  // exact for r < 256, pack <= 16
-    a.tile_tokens = p->tile_tokens;
-    a.head_groups = c.num_q_heads / p->pack;
-    a.scale_log2 = (float)((double)p->scale * 1.4426950408889634);
-    a.xcd_remap = env_xcd_remap();
     if (rope) {
         a.k_rope = (const u16*)rope->k_rope;
         a.kr_st = (int32_t)rope->kr_st;

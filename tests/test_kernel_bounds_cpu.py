@@ -1,13 +1,14 @@
-"""Host model of the attention kernel's indexing, checked on the CPU for many plans.
+"""Host model of the attention kernel's key-tile copies, checked on the CPU for many plans.
 
-The launch runs num_slots x num_heads workgroups; a workgroup reads work-list
-entries 2*slot and 2*slot + 1, runs the first entry's key tiles ascending and the
-second's descending. Per tile loop it issues the copies of the key tiles of visits
+The tiles are those that plan_items lists: entries 2*slot and 2*slot + 1 are a work
+slot's tiles, the first with its keys ascending, the second descending
+(test_launch_replay_cpu.py shows that the listed tiles with keys are the launched ones).
+Per tile loop a workgroup issues the copies of the key tiles of visits
 0 and 1 up front, then in step t the K copy of visit t+2 and the V copy of visit
 t+1, through the same running values the kernel keeps (first key of the K copy,
 visits left). This model replays exactly those updates and checks that
 
-* every work-list read is inside the list;
+* the listing has two entries for every slot;
 * every copy with rows reads only keys inside its entry's range [key_begin, key_end)
   (so cache rows stay inside the cache the plan was checked against);
 * every key of the range is copied exactly once for K and once for V, and each visit
@@ -75,7 +76,7 @@ def _check_plan(cfg, cu, kvs, pre):
         B.vpp_chunk_attn_destroy(h)
     n = len(items)
     assert info.num_slots * 2 == n
-    # the grid: every workgroup's entries are inside the list
+    # every slot's entries are inside the list
     for slot in range(info.num_slots):
         for sub in (0, 1):
             e = 2 * slot + sub
