@@ -223,12 +223,14 @@ struct Launch {
     CombineArgs merge;
     CombineTable segs;
     int32_t nb, dqk;
-    // Whether most of the launch's key steps are of segments with one tile a head group,
+    // Whether most of the launch's key steps are of segments with one tile a kv head,
     // whose K/V tiles no other workgroup reads: their copies are then non-temporal
     // (128-row tiles only, which such launches use). Single tokens behind 4K to 23K
     // cached ones: 64 of 32/8 heads 635 -> 578 us, 16 of 16 MLA heads 194 -> 176; a
     // serving step with a 480-row prompt piece 257 -> 233. Where tiles share their keys
-    // it costs 1.5 to 6 % (six short prompts 233 -> 247), the L2 keeping them too briefly.
+    // it costs time, the L2 keeping them too briefly: the tiles of a segment 1.5 to 6 %
+    // (six short prompts 233 -> 247), the head groups of a kv head whose heads do not fit
+    // one tile 5 to 19 % (32 single tokens of 32/1 heads 64 -> 75, of 71/1 791 -> 894).
     bool nt;
     int64_t workgroups;
 };
@@ -1707,7 +1709,7 @@ int64_t longest_slot(const SegPlan& s, int tt, int32_t begin, int32_t end) {
 // pieces of every segment's prefix. The choice is the one whose launch this model
 // finishes first. Its constants are measured on one MI355X with normal operands.
 struct LaunchModel {
-    int heads, pack, dqk, dv;
+    int heads, kv_heads, pack, dqk, dv;
     static constexpr int NUM_CU = 256, NXCD = 8;
 
     // One 64-key step of a workgroup takes `few` us while few of them run and `full` us
@@ -1750,11 +1752,12 @@ struct LaunchModel {
     double steps(const SegPlan& s, int nb) const {
         return s.key_steps + (double)s.tiles * s.pieces * tile(nb);
     }
-    // Bytes of distinct keys and values a launch reads.
+    // Bytes of distinct keys and values a launch reads: once a kv head, also where its heads
+    // take several tiles.
     double key_bytes(const std::vector<SegPlan>& segs) const {
         double rows = 0.0;
         for (const SegPlan& s : segs) rows += (double)s.prefix + s.len;
-        return rows * (heads / pack) * (dqk + dv) * 2.0;
+        return rows * kv_heads * (dqk + dv) * 2.0;
     }
     // The time no launch of `all` steps of its workgroups comes under: the most steps per us
     // that any number of workgroups makes, and the rate of its keys.
@@ -1861,6 +1864,10 @@ struct LaunchModel {
     }
 };
 
+LaunchModel launch_model(const vpp_chunk_attn_config_t& c, int pack) {
+    return {c.num_q_heads, c.num_kv_heads, pack, c.head_dim_qk, c.head_dim_v};
+}
+
 // A candidate plan and its modelled time.
 struct Candidate {
     std::vector<SegPlan> segs;
@@ -1884,7 +1891,7 @@ Candidate choose_plan(const vpp_chunk_attn_config_t& c, const std::vector<SegPla
                       size_t max_part) {
     constexpr int MAX_PIECES = 64;
     constexpr int64_t MIN_PIECE = 4 * BN;  // keys of prefix a piece holds at least
-    const LaunchModel model{c.num_q_heads, pack, c.head_dim_qk, c.head_dim_v};
+    const LaunchModel model = launch_model(c, pack);
     const int64_t groups = c.num_q_heads / pack;
     int64_t max_prefix = 0;
     for (const SegPlan& s : segs) max_prefix = std::max<int64_t>(max_prefix, s.prefix);
@@ -2164,7 +2171,7 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
     p->nb = nb;
     p->pack = pack;
     p->tile_tokens = tt;
-    p->nt = nb == 1 && lone_steps > 0.5 * key_steps;
+    p->nt = nb == 1 && pack == c.num_q_heads / c.num_kv_heads && lone_steps > 0.5 * key_steps;
     p->scale = c.softmax_scale > 0.f ? c.softmax_scale : (float)(1.0 / sqrt((double)c.head_dim_qk));
     p->segs.swap(plan.segs);
     p->groups.swap(groups);

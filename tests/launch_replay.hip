@@ -87,3 +87,4 @@ extern "C" int64_t replay_merge(vpp_chunk_attn_plan_t p, int64_t* out) {
 
 extern "C" int replay_row_token(int r, int pack) { return row_token(r, (65536 + pack - 1) / pack); }
 extern "C" int replay_merge_ways(int pieces) { return merge_ways(pieces); }
+extern "C" double replay_key_bytes(vpp_chunk_attn_plan_t p) { return launch_model(p->cfg, p->pack).key_bytes(p->segs); }

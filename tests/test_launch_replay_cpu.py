@@ -38,7 +38,7 @@ def lib(tmp_path_factory):
     vp = ctypes.c_void_p
     for name, args, ret in (("replay_summary", [vp, vp], None), ("replay_groups", [vp, vp], None),
                             ("replay_merges", [vp, vp], None), ("replay_tiles", [vp, vp], ctypes.c_int64),
-                            ("replay_merge", [vp, vp], ctypes.c_int64)):
+                            ("replay_merge", [vp, vp], ctypes.c_int64), ("replay_key_bytes", [vp], ctypes.c_double)):
         getattr(x, name).argtypes, getattr(x, name).restype = args, ret
     return x
 
@@ -68,6 +68,7 @@ class Replay:
         self.tiles = tiles[:lib.replay_tiles(h, tiles.ctypes.data)]
         pairs = np.zeros((self.merge_blocks * (1024 // dv), 3), dtype=np.int64)
         self.pairs = pairs[:lib.replay_merge(h, pairs.ctypes.data)]
+        self.key_bytes = lib.replay_key_bytes(h)
         n = ctypes.c_int32(0)
         assert lib.vpp_chunk_attn_plan_items(h, None, 0, ctypes.byref(n)) == B.VPP_OK
         self.items = np.zeros(n.value, dtype=B.WORK_ITEM_DTYPE)
@@ -204,3 +205,17 @@ def test_row_token_is_the_division(lib):
     for pack in range(1, 17):
         for row in range(256):
             assert lib.replay_row_token(row, pack) == row // pack
+
+
+# heads per kv head: 1, 4, 16 fit one tile; 17, 24, 32 and 71 take several, which read the same keys
+@pytest.mark.parametrize("hq,hkv,one_tile", [(16, 16, True), (32, 8, True), (64, 4, True), (4, 1, True), (17, 1, False),
+                                             (34, 2, False), (24, 1, False), (64, 2, False), (71, 1, False)])
+@pytest.mark.parametrize("dqk,dv", [(64, 64), (128, 128), (192, 128)])
+def test_keys_read_by_one_workgroup(lib, hq, hkv, one_tile, dqk, dv):
+    """Non-temporal copies only of keys that one workgroup reads, and every kv head's keys counted once."""
+    lens, pre = [1] * 32, [4096 + 600 * i for i in range(32)]
+    r = check(lib, hq, hkv, dqk, dv, lens, pre)
+    t = r.tiles
+    readers = np.unique(np.stack([t[:, ENTRY], t[:, HK], t[:, KB]], axis=1), axis=0, return_counts=True)[1]
+    assert r.nt == one_tile == (readers.max() == 1)
+    assert r.key_bytes == (sum(pre) + sum(lens)) * hkv * (dqk + dv) * 2
