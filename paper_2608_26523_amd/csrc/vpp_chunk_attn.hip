@@ -146,7 +146,7 @@ struct LaunchGroup {
     int32_t prefix;     // in-request position of the first row
     int32_t kv_start;   // cache row of the request's position 0
     int32_t seg;        // block-table row (paged cache)
-    int32_t pieces;     // split pieces of the prefix (piece_begin)
+    int32_t pieces;     // split pieces of the prefix (piece_begin); negative: last_pieces_first
     int32_t part0;      // first row of piece 0's fp32 partials; < 0: final results
     int32_t slots;      // work slots per head group and piece: two tiles, or one when slots == tiles
     int32_t tiles;      // query tiles per head group
@@ -358,16 +358,16 @@ __device__ __forceinline__ int find_entry(uint64_t table, int stride, int n, int
     return __builtin_amdgcn_readfirstlane(e.lo);
 }
 
-// Workgroup i of a group -> (slot, head), `heads` counting split pieces too (the
-// pieces of a head follow each other). Consecutive workgroups land on the 8 XCDs
-// round robin. Slots of two tiles (paired) are alike: each XCD gets a contiguous run
-// of the group's head-major order, the slots of the same heads, which read the same
-// K/V through that XCD's L2. Slots of one tile grow with their index: the XCDs that
-// share a head take turns at its slots, longest first (contiguous runs gave one XCD
-// the short half and the next the long half of a causal segment: 1120 us where pairs
-// take 984, at 6915 rows and 64/4 heads). Every group is spread over all XCDs.
-__host__ __device__ __forceinline__ void work_coords(int i, int slots, int heads, bool paired, bool remap, int& slot, int& head) {
-    if (remap && paired) {
+// Workgroup i of a run of slots -> (slot, head); `heads` counts pieces too (the pieces of
+// a head follow each other). Consecutive workgroups land on the 8 XCDs round robin.
+// Where the slots are alike (two tiles each, or pieces without the tiles' own keys), each
+// XCD gets a contiguous run of the head-major order, the slots of the same heads, which
+// read the same K/V through that XCD's L2. Slots of one tile grow with their index: the
+// XCDs that share a head take turns at its slots, longest first (contiguous runs gave one
+// XCD the short half and the next the long half of a causal segment: 1120 us where pairs
+// take 984, at 6915 rows and 64/4 heads). Every run is spread over all XCDs.
+__host__ __device__ __forceinline__ void work_coords(int i, int slots, int heads, bool alike, bool remap, int& slot, int& head) {
+    if (remap && alike) {
         const int n = slots * heads;
         const int x = i & 7;
         i = x * (n >> 3) + min(x, n & 7) + (i >> 3);
@@ -377,7 +377,7 @@ __host__ __device__ __forceinline__ void work_coords(int i, int slots, int heads
     }
     head = slots == 1 ? i : i / slots;
     slot = i - head * slots;
-    if (!paired) slot = slots - 1 - slot;
+    if (!alike) slot = slots - 1 - slot;
 }
 
 // Token of a tile's row r, r < 256 (AttnArgs::pack_magic).
@@ -390,17 +390,32 @@ struct TileWork {
     int key_begin, key_end;       // keys of the request that this piece covers
     int out_row0;                 // where the results go: row0, or ~ the first partial row
 };
+struct TileArgs {  // of AttnArgs
+    int32_t group, pack, tile_tokens, head_groups, xcd_remap;
+};
 // false: the workgroup has no such tile. `block` counts from the group's first workgroup.
-template <typename Args, typename Group>
-__host__ __device__ __forceinline__ bool tile_work(const Args& a, const Group& g, int block, int sub, TileWork& w) {
-    const int slots = g.slots, seg_tiles = g.tiles, pieces = g.pieces;
+__host__ __device__ __forceinline__ bool tile_work(const TileArgs& a, const LaunchGroup& g, int block, int sub, TileWork& w) {
+    const int slots = g.slots, seg_tiles = g.tiles, pieces = abs(g.pieces);
     const bool paired = slots != seg_tiles;
+    // the run's pieces: `per` of them, from `top` down (the last piece is the longest: first)
+    int top = pieces - 1, per = pieces;
+    bool alike = paired;
+    if (g.pieces < 0) {  // two runs: the last pieces of all head groups, then the others
+        const int last = slots * a.head_groups;
+        if (block < last) {
+            per = 1;
+        } else {
+            block -= last;
+            --top, --per;
+            alike = true;
+        }
+    }
     int slot, hg, piece = 0, piece_kb = 0, piece_ke = INT32_MAX;  // hg: head group
-    work_coords(block, slots, a.head_groups * pieces, paired, a.xcd_remap != 0, slot, hg);
+    work_coords(block, slots, a.head_groups * per, alike, a.xcd_remap != 0, slot, hg);
     if (pieces > 1) {
         const int hp = hg;
-        hg = hp / pieces;
-        piece = pieces - 1 - (hp - hg * pieces);  // the last piece is the longest: first
+        hg = hp / per;
+        piece = top - (hp - hg * per);
         piece_kb = piece_begin(g.prefix, pieces, piece);
         if (piece + 1 < pieces) piece_ke = piece_begin(g.prefix, pieces, piece + 1);
     }
@@ -793,10 +808,17 @@ void attn_fwd_kernel(AttnArgs args, GroupTable) {
         asm volatile("" : "+s"(gidx), "+s"(ap));
         const_args_t& a = *ap;
         const_group_t* const grp = const_ptr<const_group_t>(group_base(a.groups)) + gidx;
+        // read at once (the empty asm needs them all here): left to the compiler, each is
+        // read where it is first used, five latencies in a row
+        LaunchGroup g{grp->wg0, grp->row0, grp->len, grp->prefix, grp->kv_start, grp->seg, grp->pieces, grp->part0, grp->slots, grp->tiles};
+        TileArgs ta{a.group, a.pack, a.tile_tokens, a.head_groups, a.xcd_remap};
+        asm volatile("" : "+s"(g.wg0), "+s"(g.row0), "+s"(g.len), "+s"(g.prefix), "+s"(g.kv_start), "+s"(g.pieces), "+s"(g.part0),
+                          "+s"(g.slots), "+s"(g.tiles), "+s"(ta.group), "+s"(ta.pack), "+s"(ta.tile_tokens),
+                          "+s"(ta.head_groups), "+s"(ta.xcd_remap));
         TileWork it;
-        if (!tile_work(a, *grp, (int)blockIdx.x - grp->wg0, sub, it)) break;
+        if (!tile_work(ta, g, (int)blockIdx.x - g.wg0, sub, it)) break;
         const int h = it.h, hk = it.hk, out_row0 = it.out_row0;
-        const int64_t kv_start = grp->kv_start;
+        const int64_t kv_start = g.kv_start;
         // every wave is done with the LDS tiles of the slot's previous tile before
         // this tile's first copies overwrite them
         lds_barrier();
@@ -819,7 +841,7 @@ void attn_fwd_kernel(AttnArgs args, GroupTable) {
         const int dkt = rev ? -BN : BN;
         const int kt_first = rev ? kb + (ntiles - 1) * BN : kb;
         // paged cache: this segment's block-table row and the cache row of key 0
-        const int32_t* bt_row = PAGED ? a.block_table + (int64_t)grp->seg * a.bt_st : nullptr;
+        const int32_t* bt_row = PAGED ? a.block_table + (int64_t)g.seg * a.bt_st : nullptr;
         const int kv_off = PAGED ? (int)kv_start : 0;
         const int pmask = PAGED ? (1 << a.page_shift) - 1 : 0;
         const int last_row = kv_off + ke - 1;  // page reads past the key range are clamped here
@@ -1281,6 +1303,10 @@ void attn_fwd_kernel(AttnArgs args, GroupTable) {
             // last pair computes one S^T tile too many, from stale LDS data, and
             // discards it: cheaper than a third step variant's registers.
             int t = 0;
+            // Where the loop starts in its 64-byte line of code decides up to 1 % at these
+            // sizes (16384 rows behind 507904, 16 MLA heads: 65.6 ms at 16 of 64, 66.5 at 8,
+            // 65.9 at 24); two instructions follow before it.
+            if constexpr (DQK == 192 && NB == 2) asm volatile(".p2align 6\n\ts_nop 0\n\ts_nop 0");
             for (; t + 1 < ntiles; t += 2) {
                 step(P0(), NX(), t, s_a, s_b);
                 step(P1(), NX(), t + 1, s_b, s_a);
@@ -1704,6 +1730,18 @@ int64_t longest_slot(const SegPlan& s, int tt, int32_t begin, int32_t end) {
     return best;
 }
 
+// Whether a split segment's last pieces, which end with the tiles' own keys, are a run of
+// their own, before the other pieces. In one run of all pieces the XCDs get the last pieces
+// of whole head groups, so some XCDs work longer where those are no multiple of the XCDs:
+// the line is a quarter more than the mean. us in one run and in two: 6089 rows of 4/1
+// heads behind 1539 keys in 8 pieces 268 and 132, 2000 behind 16000 118 and 93; 2645 of
+// 24/2 heads behind 2959 in 4 pieces 271 and 199. Below the line both are alike (217 rows of
+// 4/1 heads behind 32768 34.2 and 33.7, 600 behind 16000 48.7 and 49.2).
+bool last_pieces_first(const SegPlan& s, int64_t head_groups) {
+    const int64_t most = (head_groups + 7) / 8 * 8;  // 8 times the head groups of the fullest XCD
+    return s.pieces > 1 && 4 * (most - head_groups) * s.len > head_groups * ((int64_t)s.prefix + s.len);
+}
+
 // ---- launch model -----------------------------------------------------------
 // What a plan may choose: the tile variant, one or two tiles per work slot, and the
 // pieces of every segment's prefix. The choice is the one whose launch this model
@@ -1780,26 +1818,27 @@ struct LaunchModel {
         double even = 0.0;               // steps every place has had alike
         double placed = 0.0, top = 0.0;  // beside those: the mean and the most of a place
         int64_t seen = 0;
-        for (const SegPlan& s : segs) {
-            const int64_t n = s.slots() * groups * s.pieces;
+        // `count` pieces of a segment from `piece` down, one run of slots (tile_work): `own`
+        // steps of one place, `longest` of one slot.
+        auto run = [&](const SegPlan& s, int piece, int count, double own, double longest) {
+            const int64_t h = groups * count, n = s.slots() * h;
             int64_t share = (seen + n + NXCD - 1) / NXCD - (seen + NXCD - 1) / NXCD;
             seen += n;
-            // While twice a segment's longest slot and what the fullest place is ahead are
+            // While twice a run's longest slot and what the fullest place is ahead are
             // still to come on every place, the shorter slots behind even out whatever the
-            // segment's own placing would leave uneven.
-            const double own = steps(s, nb) * groups / (NXCD * places);
+            // run's own placing would leave uneven.
             left -= own;
             const bool evens_out = top - placed <= left;
-            if (evens_out && 2.0 * ((double)s.longest / BN + 2.0 * c_tile) < left) {
+            if (evens_out && 2.0 * longest < left) {
                 even += own;
-                continue;
+                return;
             }
             placed += own;
-            // every `stride`-th slot of its heads, longest first where slots are single tiles
-            const int64_t h = groups * s.pieces;
-            const int stride = s.paired ? 1 : (int)(NXCD / std::min<int64_t>(NXCD, h & -h));
+            // its slots in order, or every `stride`-th of its heads, longest first
+            const bool alike = s.paired || piece < s.pieces - 1;  // a run without last pieces
+            const int stride = alike ? 1 : (int)(NXCD / std::min<int64_t>(NXCD, h & -h));
             const int64_t all = share;
-            // many rounds of one segment fill the places evenly: only a few are placed,
+            // many rounds of one run fill the places evenly: only a few are placed,
             // taken evenly from its slots
             if (share > (evens_out ? 5 : 8) * places) {
                 share = share % places + 4 * places;
@@ -1807,16 +1846,16 @@ struct LaunchModel {
                 even += spread;
                 placed -= spread;
             }
-            if (share == 0) continue;
-            // slot i of a head group, piece by piece from the last on, in launch order
-            const int64_t ring = (int64_t)s.slots() * s.pieces;
+            if (share == 0) return;
+            // slot i of a head group, piece by piece, in launch order
+            const int64_t ring = (int64_t)s.slots() * count;
             auto cost = [&](int64_t i) {
-                const int b = (int)(i / s.slots()), at = (int)(i - (int64_t)b * s.slots()), piece = s.pieces - 1 - b;
-                const int32_t kb = s.pieces == 1 ? 0 : piece_begin(s.prefix, s.pieces, piece);
-                const int32_t ke = b == 0 ? INT32_MAX : piece_begin(s.prefix, s.pieces, piece + 1);
+                const int b = (int)(i / s.slots()), at = (int)(i - (int64_t)b * s.slots());
+                const int32_t kb = s.pieces == 1 ? 0 : piece_begin(s.prefix, s.pieces, piece - b);
+                const int32_t ke = piece - b == s.pieces - 1 ? INT32_MAX : piece_begin(s.prefix, s.pieces, piece - b + 1);
                 double t = 0.0;
                 for (int which = 0; which < 2; ++which) {
-                    const int tl = slot_tile(s, s.paired ? at : s.slots() - 1 - at, which);
+                    const int tl = slot_tile(s, alike ? at : s.slots() - 1 - at, which);
                     if (tl >= 0) t += (double)((tile_keys(s, tt, tl, kb, ke) + BN - 1) / BN) + c_tile;
                 }
                 return t;
@@ -1847,6 +1886,20 @@ struct LaunchModel {
                 }
                 if (i >= ring) i = i < 2 * ring ? i - ring : i % ring;
             }
+        };
+        const double per_place = (double)groups / (NXCD * places);
+        for (const SegPlan& s : segs) {
+            const double all = steps(s, nb) * per_place, longest = (double)s.longest / BN + 2.0 * c_tile;
+            if (!last_pieces_first(s, groups)) {
+                run(s, s.pieces - 1, s.pieces, all, longest);
+                continue;
+            }
+            // the keys before the last piece are the same in every tile
+            const int others = s.pieces - 1;
+            const double before = (double)(piece_begin(s.prefix, s.pieces, others) / BN);
+            const double rest = s.tiles * (before + others * c_tile) * per_place;
+            run(s, others, 1, all - rest, longest);
+            run(s, others - 1, others, rest, 2.0 * (before / others + 1.0 + c_tile));
         }
         double steps = 0.0;
         for (double& l : lanes) steps += (l += even) * NXCD;
@@ -2142,6 +2195,7 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
         // writes its results directly
         for (const SegPlan& s : plan.segs) {
             LaunchGroup g{(int32_t)wgs, s.row0, s.len, s.prefix, s.kv_start, s.seg, s.pieces, -1, s.slots(), s.tiles};
+            if (last_pieces_first(s, c.num_q_heads / pack)) g.pieces = -s.pieces;
             if (s.pieces > 1) {
                 g.part0 = (int32_t)part_rows;
                 merges.push_back({(int32_t)blocks, s.row0, s.len, s.pieces, (int32_t)part_rows});

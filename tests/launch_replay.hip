@@ -52,13 +52,14 @@ extern "C" void replay_merges(vpp_chunk_attn_plan_t p, int32_t* out) {
 extern "C" int64_t replay_tiles(vpp_chunk_attn_plan_t p, int32_t* out) {
     AttnArgs a{};
     plan_args(p, a);
+    const TileArgs t{a.group, a.pack, a.tile_tokens, a.head_groups, a.xcd_remap};
     int64_t n = 0;
     for (int block = 0; block < p->workgroups; ++block) {
         const int e = find_on_host(a.num_groups, block, [&](int i) { return p->groups.at((size_t)i).wg0; });
         const LaunchGroup& g = p->groups.at((size_t)e);
         for (int sub = 0; sub < 2; ++sub) {
             TileWork w;
-            if (!tile_work(a, g, block - g.wg0, sub, w)) break;
+            if (!tile_work(t, g, block - g.wg0, sub, w)) break;
             const int32_t row[] = {block, e, sub, w.h, w.hk, w.row0, w.nrows, w.pos0, w.key_begin, w.key_end, w.out_row0};
             std::copy(std::begin(row), std::end(row), out + 11 * n++);
         }

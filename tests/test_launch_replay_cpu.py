@@ -91,6 +91,7 @@ def check(lib, hq, hkv, dqk, dv, lens, pre, splits=-1, kvs=None):
     r = Replay(lib, hq, hkv, dqk, dv, lens, pre, splits, kvs)
     t, g = r.tiles, r.groups
     wg0, row0, length, prefix, kv_start, seg, pieces, part0, slots, ntiles = g.T.astype(np.int64)
+    pieces = abs(pieces)  # negative: the last pieces are a run of their own
     # the table: one entry per segment with rows
     assert sorted(seg) == [s for s in range(len(lens)) if lens[s] > 0]
     assert (row0 == r.cu[seg]).all() and (length == np.diff(r.cu)[seg]).all()
@@ -137,8 +138,8 @@ def check(lib, hq, hkv, dqk, dv, lens, pre, splits=-1, kvs=None):
     assert (part == part0[e[split]] + b * length[e[split]] + ti[split] * r.tt).all()
     assert (b >= 0).all() and (b < pieces[e[split]]).all()
     # the merge: the split segments, each pair once a way
-    merged = g[pieces > 1]
-    assert (r.merges[:, 1:] == merged[:, [1, 2, 6, 7]]).all()
+    merged = np.stack([row0, length, pieces, part0], axis=1)[pieces > 1]
+    assert (r.merges[:, 1:] == merged).all()
     assert _once(r.pairs)
     ways = np.array([lib.replay_merge_ways(int(n)) for n in r.merges[:, 3]], dtype=np.int64)
     assert len(r.pairs) == (ways * r.merges[:, 2].astype(np.int64) * hq).sum()
@@ -219,3 +220,16 @@ def test_keys_read_by_one_workgroup(lib, hq, hkv, one_tile, dqk, dv):
     readers = np.unique(np.stack([t[:, ENTRY], t[:, HK], t[:, KB]], axis=1), axis=0, return_counts=True)[1]
     assert r.nt == one_tile == (readers.max() == 1)
     assert r.key_bytes == (sum(pre) + sum(lens)) * hkv * (dqk + dv) * 2
+
+
+# few head groups: rows of one segment in fixed pieces, whose last piece is long (its own keys)
+@pytest.mark.parametrize("hq,hkv,dqk,dv,rows,pre,splits", [
+    (4, 1, 128, 128, 6089, 1539, 8), (4, 1, 128, 128, 6089, 1539, 16), (16, 1, 64, 64, 4000, 2000, 4),
+    (8, 2, 128, 128, 5000, 1000, 4), (3, 3, 64, 64, 3000, 700, 5), (9, 9, 64, 64, 3000, 700, 4),
+])
+def test_long_pieces_are_spread_over_the_xcds(lib, hq, hkv, dqk, dv, rows, pre, splits):
+    r = check(lib, hq, hkv, dqk, dv, [rows], [pre], splits)
+    assert abs(r.groups[0, 6]) == splits
+    steps = -(-(r.tiles[:, KE] - r.tiles[:, KB]) // 64).astype(np.int64)
+    load = np.bincount(r.tiles[:, BLOCK] & 7, weights=steps, minlength=8)
+    assert load.max() <= 1.25 * load.mean()
