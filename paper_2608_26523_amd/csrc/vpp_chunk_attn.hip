@@ -1416,18 +1416,18 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, CombineTabl
     const float* const po = a.part_o + ((int64_t)sg->part0 * a.num_heads + at) * DV + c * 4;
     float mx = -INFINITY, den = 0.f;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int b0 = way; b0 < n; b0 += 4 * ways) {
+    // Four pieces in flight. Past the last one: weight 0, and zeros, nothing being read there
+    // (0 times an infinite partial would be NaN; reading piece b0 again cost 2 to 4 us a call,
+    // 1500 rows of 16 heads behind 16000 keys in 8 pieces 245.3 and 241.9).
+    auto four = [&](int b0, auto whole) {
         float l[4];
         float4 v[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {  // four pieces in flight
-            // past the last one: weight 0, and zeros (it would make NaN of an infinite partial).
-            // Nothing is read there: reading piece b0 again cost 2 to 4 us a call (1500 rows of
-            // 16 heads behind 16000 keys in 8 pieces 245.3 and 241.9).
+        for (int j = 0; j < 4; ++j) {
+            const int64_t b = b0 + j * ways;
             l[j] = -INFINITY;
             v[j] = {0.f, 0.f, 0.f, 0.f};
-            const int64_t b = b0 + j * ways;
-            if (b < n) {
+            if (whole || b < n) {
                 l[j] = pl[b * pairs];
                 v[j] = *(const float4*)(po + b * pairs * DV);
             }
@@ -1447,7 +1447,10 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a, CombineTabl
             acc[3] += w * v[j].w;
         }
         mx = m;
-    }
+    };
+    int first = 0;  // the same in all lane groups of a row: a wave takes one of the two
+    for (; first + 4 * ways <= n; first += 4 * ways) four(first + way, std::true_type());
+    if (first < n) four(first + way, std::false_type());
     if (ways > 1) {  // the block's segment decides: uniform
         __shared__ float4 s_acc[256];
         __shared__ float2 s_md[GROUPS];
