@@ -2187,7 +2187,7 @@ extern "C" vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg, 
             plan = choose_plan(c, segs, nb_mask, pack, SIZE_MAX);
             // a chunk that one-head tiles in pairs would keep within the scratch of
             // run_noalloc stays within it
-            const size_t table = std::max<size_t>(4u << 20, align256(segs.size() * (sizeof(LaunchGroup) + sizeof(CombineSeg))));
+            const size_t table = align256(segs.size() > INLINE_GROUPS ? segs.size() * (sizeof(LaunchGroup) + sizeof(CombineSeg)) : 1);
             const size_t room = (size_t)VPP_NOALLOC_SCRATCH_BYTES - std::min<size_t>(table, VPP_NOALLOC_SCRATCH_BYTES);
             if (c.num_splits < 1 && partial_bytes(c, plan.part_rows()) > room) {
                 const int one_head_nb = forced_nb() ? forced_nb() : small ? 1 : 2;

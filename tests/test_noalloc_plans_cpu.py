@@ -86,3 +86,11 @@ def test_many_segments_of_which_one_is_split(hq, hkv, nseg, prefix, others):
     ws, info = _plan(hq, hkv, 128, 128, [1] * nseg, [prefix] + [others] * (nseg - 1), -1)
     partials = sum(_a(info.num_splits * hq * x * 4) for x in (128, 1)) if others == 0 else 1 << 20
     assert ws <= max(60 * nseg + 256 + partials, 1 << 20)
+
+
+def test_partials_may_fill_the_scratch():
+    """Only a launch table, past 64 segments, is taken off the room for partials: 3 pieces, which the
+    former planner took here, need 61.3 MiB of the 64."""
+    ws, info = _plan(12, 4, 64, 64, [6865], [96676], -1)
+    assert info.num_splits == 3
+    assert ws <= B.NOALLOC_SCRATCH_BYTES
