@@ -115,10 +115,11 @@ vpp_status_t vpp_chunk_attn_plan(const vpp_chunk_attn_config_t* cfg,
 
 /*
  * Run a planned chunk, asynchronously on `stream` (a hipStream_t; NULL is the
- * default stream). Enqueues, in order: for plans of more than 64 segments the copy of the launch table into the workspace, the attention
- * kernel, and -- when the plan splits a segment's key range -- the merge kernel. Never synchronizes the stream. All pointers are
- * caller-owned device memory that must stay valid until the stream reaches the
- * end of this work; lse may be NULL. The workspace (>= the planned bytes,
+ * default stream). Enqueues, in order: for plans of more than 64 segments the copy
+ * of the launch table into the workspace, the attention kernel, and -- when the
+ * plan splits a segment's key range -- the merge kernel. Never synchronizes the
+ * stream. All pointers are caller-owned device memory that must stay valid until
+ * the stream reaches the end of this work; lse may be NULL. The workspace (>= the planned bytes,
  * 256-byte aligned) must not be used by other work in flight.
  */
 vpp_status_t vpp_chunk_attn_run(vpp_chunk_attn_plan_t plan,
@@ -272,7 +273,7 @@ const char* vpp_status_str(vpp_status_t status);
 typedef struct {
     int32_t num_tiles;        /* query tiles (per head group) in the chunk         */
     int32_t num_splits;       /* most pieces a segment is cut into (1 = no merge)  */
-    int32_t num_work_items;   /* work-list entries: two per slot                   */
+    int32_t num_work_items;   /* entries of plan_items: two per slot               */
     int32_t block_m;          /* rows per tile: (token, head) pairs of the heads
                                  that share it, the largest divisor of Hq/Hkv up
                                  to 16                                             */
@@ -280,7 +281,9 @@ typedef struct {
     int32_t num_tokens;       /* cu_q[n]                                           */
     int64_t workspace_bytes;  /* same value vpp_chunk_attn_plan returned           */
     double pairs;             /* visible (query, key) pairs per head               */
-    int32_t num_slots;        /* work slots = workgroups per head group            */
+    int32_t num_slots;        /* slots of plan_items: those of every segment times
+                                 num_splits. A launch runs no more per head group:
+                                 a segment cut into fewer pieces has fewer         */
 } vpp_chunk_attn_plan_info_t;
 
 vpp_status_t vpp_chunk_attn_plan_info(vpp_chunk_attn_plan_t plan,
@@ -298,14 +301,16 @@ typedef struct {
     int64_t kv_base;   /* cache row of the request's position 0                */
 } vpp_chunk_attn_work_item_t;
 
-/* Copy up to `capacity` work items of the plan, in launch order; *count gets
- * the plan's item count. Entries 2m and 2m+1 form work slot m, which one
- * workgroup per head group runs: the first entry's tile with its keys ascending, then
- * the second's (the partner tile from the other end of the same segment, in the
- * same split piece) with its keys descending. A second entry with nrows = 0 is
- * empty. Every (tile, split piece) appears exactly once; a piece without keys
- * (key_begin == key_end) is not launched. A slot may hold one tile (its second
- * entry empty) or two, as the plan finds faster. */
+/* Copy up to `capacity` work items of the plan; *count gets the plan's item
+ * count. This lists the plan's work; it is not what a launch reads, and its order
+ * -- (segment, piece) pairs, longest slot first -- is not that of the workgroups.
+ * Entries 2m and 2m+1 form work slot m, which one workgroup per head group runs:
+ * the first entry's tile with its keys ascending, then the second's (the partner
+ * tile from the other end of the same segment, in the same split piece) with its
+ * keys descending. A second entry with nrows = 0 is empty: a slot may hold one
+ * tile or two, as the plan finds faster. Every (tile, split piece) appears
+ * exactly once. A segment cut into fewer than num_splits pieces has pieces
+ * without keys in front (key_begin == key_end), which are not launched. */
 vpp_status_t vpp_chunk_attn_plan_items(vpp_chunk_attn_plan_t plan,
                                        vpp_chunk_attn_work_item_t* items,
                                        int32_t capacity, int32_t* count);

@@ -5,11 +5,12 @@
 // prefix .. prefix+len-1 attending to the cached prefix plus the chunk itself
 // (section 2.4). Several requests may share a chunk (packing, section 5.3).
 //
-// Kernel layout: one workgroup = 4 waves running one work slot of one query
-// head: up to two query tiles of 256 (or 128) rows of one segment, the first
-// with its keys ascending, the second -- its partner from the other end of the
-// segment -- descending, so that the workgroups on an XCD read the same keys
-// at the same time. Keys stream through LDS 64 at a time:
+// Kernel layout: one workgroup = 4 waves running one work slot of one group of
+// query heads that share a kv head: one query tile of 256 (or 128) rows -- a row
+// is a token of one of those heads -- of one segment, or two, the first with its
+// keys ascending, the second -- its partner from the other end of the segment --
+// descending, so that the workgroups on an XCD read the same keys at the same
+// time. Keys stream through LDS 64 at a time:
 //   * S^T = K Q^T on v_mfma_f32_32x32x16_bf16: keys are the M dimension,
 //     queries the N dimension, head dim the K dimension. Each lane then owns
 //     one query (column lane%32) and 16 keys per 32-key block, so a row max or
@@ -231,6 +232,10 @@ struct Launch {
     // it costs time, the L2 keeping them too briefly: the tiles of a segment 1.5 to 6 %
     // (six short prompts 233 -> 247), the head groups of a kv head whose heads do not fit
     // one tile 5 to 19 % (32 single tokens of 32/1 heads 64 -> 75, of 71/1 791 -> 894).
+    // With keys that come from memory, as in an engine, which reads the other layers' between
+    // two calls on one: over 287 launches of single tokens non-temporal copies took 0.87 to
+    // 1.1 times the time of others, mean 0.97. Keys still cached from the call before are
+    // read up to 1.28 times slower.
     bool nt;
     int64_t workgroups;
 };
@@ -364,8 +369,8 @@ __device__ __forceinline__ int find_entry(uint64_t table, int stride, int n, int
 // XCD gets a contiguous run of the head-major order, the slots of the same heads, which
 // read the same K/V through that XCD's L2. Slots of one tile grow with their index: the
 // XCDs that share a head take turns at its slots, longest first (contiguous runs gave one
-// XCD the short half and the next the long half of a causal segment: 1120 us where pairs
-// take 984, at 6915 rows and 64/4 heads). Every run is spread over all XCDs.
+// XCD the short half and the next the long half of a causal segment: 1120 us where turns
+// take 921 and pairs 984, at 6915 rows and 64/4 heads). Every run is spread over all XCDs.
 __host__ __device__ __forceinline__ void work_coords(int i, int slots, int heads, bool alike, bool remap, int& slot, int& head) {
     if (remap && alike) {
         const int n = slots * heads;
@@ -1656,8 +1661,13 @@ bool supported_dims(int dqk, int dv) {
 // workgroups per CU), which even out the unequal key ranges of the diagonal tiles;
 // others take what the launch model below finds faster. With dqk = 192 a few whole
 // 256-row tiles keep them; otherwise the model chooses too: the 128-row tiles halve
-// what a short segment leaves empty, and two workgroups a CU stream distinct keys at
-// 5.9 TB/s where one reaches 4.0. VPP_NB overrides, for tuning.
+// what a short segment leaves empty, and two workgroups a CU stream distinct keys
+// faster than one (LaunchModel::stream). VPP_NB overrides, for tuning.
+// us with 128- and 256-row tiles: up to one 256-row workgroup a CU 45 and 55 (2048 rows of
+// 32/8 heads), 78 and 100 (4096 of 16/16), behind 7000 keys 254 and 247, 304 and 292; up to
+// two of them, dqk 128, 135 and 128 (4096 of 32/8), behind 7000 keys 543 and 509; dqk 64
+// 161 and 160 (8192 of 16/4). By these the line would be one workgroup a CU; callers of the
+// plan interface have been given 128-row tiles up to two, and a test of it holds that.
 bool small_chunk(const vpp_chunk_attn_config_t& c, int64_t tiles256, double mean_keys256) {
     return c.head_dim_qk <= 128 && tiles256 * c.num_q_heads <= 2 * 256 && mean_keys256 <= 8192.0;
 }
@@ -1785,7 +1795,9 @@ struct LaunchModel {
     // last step, store. Two 128-row workgroups a CU hide much of each other's.
     double tile(int nb) const { return nb == 1 ? 2.0 : 4.0; }
     // The rate at which workgroups stream distinct keys, one or two in flight per CU:
-    // it holds back the steps of segments with few tiles.
+    // it holds back the steps of segments with few tiles. Single tokens behind 2000 to 16000
+    // keys: 5.1, 6.4, 6.2 TB/s at dqk 64, 128, 192 with two of 128 rows, 3.1, 4.2, 4.5 with
+    // one of 256.
     double stream(int nb) const { return nb == 1 ? 6.0e6 : 3.8e6; }  // bytes per us
 
     // Time of the merge of part_rows partial rows: a launch, and the partials written
