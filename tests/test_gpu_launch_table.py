@@ -73,6 +73,10 @@ def test_many_segments(nseg, rows, prefix, heads, splits):
     ((4, 1), (128, 128), [(9000, 217), (40, 300)], -1),
     ((8, 2), (128, 128), [(6000, 40), (3000, 1), (0, 700), (100, 1)], -1),
     ((16, 16), (192, 128), [(5000, 60), (700, 1)], -1),
+    # few head groups and long last pieces: launched as two runs
+    ((4, 1), (128, 128), [(200, 600)], 3),
+    ((9, 9), (64, 64), [(130, 300)], 2),
+    ((3, 1), (192, 128), [(256, 500), (64, 90), (900, 40)], 4),
 ])
 def test_pieces_and_merge(heads, dims, segs, splits):
     from paper_2608_26523_amd.attention import ChunkAttention
